@@ -131,8 +131,14 @@ hipError_t launch_sort_rows(const int32_t *d, int64_t ld, int32_t n, int32_t m,
 int eval_workgroups_per_cu(int W, bool reduced, bool paired, int waves = kEvalWaves);
 hipError_t launch_eval(const EvalArgs &a, hipStream_t s, hipEvent_t e0 = nullptr,
                        hipEvent_t e1 = nullptr);
+// Where the reduction hands over the error bits of a call that waits (now ==
+// nullptr: it does not): the word the call's kernels collect them in (zero
+// between calls), the instance's error word, a host word.
+struct ErrOut {
+    uint32_t *now = nullptr, *keep = nullptr, *host = nullptr;
+};
 hipError_t launch_reduce(const EvalArgs &a, unsigned long long *fitness,
-                         unsigned long long *scan, hipStream_t s);
+                         unsigned long long *scan, hipStream_t s, const ErrOut &eo = ErrOut{});
 // Facility-major copies of the chromosome tiles of a.masks into tg (a.P
 // chromosomes, a.t.W words each) and the feasibility check of every
 // chromosome (error bits into a.err).

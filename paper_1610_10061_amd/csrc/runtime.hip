@@ -109,6 +109,44 @@ Staging &staging()
     return st;
 }
 
+// Pinned host words, one per live instance, that a waiting evaluation's
+// error bits are stored to by its last kernel (an instance takes its word
+// when it is made, so that evaluations allocate nothing).  Pages of words
+// are kept until the process ends; words are handed out again.
+struct HostWords {
+    std::mutex mu;
+    std::vector<uint32_t *> spare;
+
+    uint32_t *take()
+    {
+        constexpr size_t kPage = 1024;
+        std::lock_guard<std::mutex> lock(mu);
+        if (spare.empty()) {
+            uint32_t *page = nullptr;
+            if (hipHostMalloc((void **)&page, sizeof(uint32_t) * kPage, hipHostMallocPortable) !=
+                hipSuccess)
+                return nullptr;
+            for (size_t k = 0; k < kPage; ++k)
+                spare.push_back(page + k);
+        }
+        uint32_t *w = spare.back();
+        spare.pop_back();
+        return w;
+    }
+    void give(uint32_t *w)
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        if (w)
+            spare.push_back(w);
+    }
+};
+
+HostWords &host_words()
+{
+    static HostWords *w = new HostWords;  // never destroyed: outlives every instance
+    return *w;
+}
+
 // Fixed-size buffers of one object carved out of a single device
 // allocation (one hipMalloc and one hipFree instead of one per buffer).
 // Members are listed with add(), then carve() allocates and assigns them;
@@ -313,6 +351,10 @@ struct pmp_instance {
     int32_t *ds = nullptr;
     int32_t *delta = nullptr;
     uint32_t *err = nullptr;
+    // error bits of the waiting evaluation under way (zero between calls),
+    // and the host word its last kernel stores them to
+    uint32_t *err_now = nullptr;
+    uint32_t *host_err = nullptr;
     // staging for host-pointer evaluation
     uint64_t *h_masks = nullptr;
     unsigned long long *h_fit = nullptr;
@@ -350,6 +392,8 @@ struct pmp_instance {
         }
         return e;
     }
+
+    ErrOut err_out() const { return ErrOut{err_now, err, host_err}; }
 
     Tables tables() const
     {
@@ -917,6 +961,7 @@ void pmp_instance_destroy(pmp_instance *inst)
     if (!inst)
         return;
     inst->arena.release();
+    host_words().give(inst->host_err);
     dfree(inst->h_masks);
     dfree(inst->h_fit);
     dfree(inst->h_scan);
@@ -967,7 +1012,7 @@ pmp_status pmp_preprocess(const int32_t *d, int64_t ld, int32_t n, int32_t m,
     inst->arena.add(&inst->pi, cells);
     inst->arena.add(&inst->ds, cells);
     inst->arena.add(&inst->delta, cells);
-    inst->arena.add(&inst->err, 1);
+    inst->arena.add(&inst->err, 64);
     inst->arena.add(&inst->colsum, (size_t)m);
     inst->arena.add(&inst->nearc, (size_t)m);
     inst->arena.add(&inst->dtotal, 2);
@@ -975,13 +1020,19 @@ pmp_status pmp_preprocess(const int32_t *d, int64_t ld, int32_t n, int32_t m,
         pmp_instance_destroy(inst);
         return fail(PMP_ENOMEM, "device allocation of tables (%zu cells)", cells);
     }
+    inst->err_now = inst->err + 32;  // (a cache line of its own)
+    inst->host_err = host_words().take();
+    if (!inst->host_err) {
+        pmp_instance_destroy(inst);
+        return fail(PMP_ENOMEM, "pinned host memory");
+    }
     int32_t *dd = nullptr;
     uint64_t *wide = nullptr;  // sort scratch of rows wider than PMP_MAX_FACILITIES
     const int32_t *src = d;
     int64_t src_ld = ld;
     pmp_status st = PMP_OK;
     do {
-        hipError_t e = hipMemsetAsync(inst->err, 0, sizeof(uint32_t), s);
+        hipError_t e = hipMemsetAsync(inst->err, 0, 64 * sizeof(uint32_t), s);
         if (e != hipSuccess) {
             st = fail(PMP_EDEVICE, "hipMemsetAsync: %s", hipGetErrorString(e));
             break;
@@ -1313,8 +1364,6 @@ pmp_status pmp_hbp_eval(pmp_hbp *hp, const uint64_t *masks, int32_t P, int64_t *
         dfit = hp->h_fit;
         dscan = scan_total ? hp->h_scan : nullptr;
     }
-    if (!async)
-        HIP_TRY(launch_zero(inst->err, sizeof(uint32_t), s));
     EvalArgs a{};
     a.t = inst->tables();
     a.t.pi = hp->rpi;
@@ -1327,7 +1376,7 @@ pmp_status pmp_hbp_eval(pmp_hbp *hp, const uint64_t *masks, int32_t P, int64_t *
     a.c0 = hp->c0;
     a.masks = dmask;
     a.P = P;
-    a.err = inst->err;
+    a.err = async ? inst->err : inst->err_now;
     a.clients_per_block = clients_per_block(hp->rows, P, inst->m, inst->p, inst->W, true);
     a.tiles_c = (P + kEvalTile - 1) / kEvalTile;
     a.tiles_i = (hp->rows + a.clients_per_block - 1) / a.clients_per_block;
@@ -1343,7 +1392,7 @@ pmp_status pmp_hbp_eval(pmp_hbp *hp, const uint64_t *masks, int32_t P, int64_t *
     a.part = hp->part;
     a.spart = dscan ? hp->spart : nullptr;
     HIP_TRY(launch_eval(a, s));
-    HIP_TRY(launch_reduce(a, dfit, dscan, s));
+    HIP_TRY(launch_reduce(a, dfit, dscan, s, async ? ErrOut{} : inst->err_out()));
     if (!on_dev) {
         HIP_TRY(hipMemcpyAsync(fitness, dfit, sizeof(int64_t) * P, hipMemcpyDeviceToHost, s));
         if (scan_total)
@@ -1352,10 +1401,8 @@ pmp_status pmp_hbp_eval(pmp_hbp *hp, const uint64_t *masks, int32_t P, int64_t *
     }
     if (async)
         return PMP_OK;
-    uint32_t herr = 0;
-    HIP_TRY(hipMemcpyAsync(&herr, inst->err, sizeof herr, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    return status_from_err(herr);
+    return status_from_err(*inst->host_err);
 }
 
 void pmp_hbp_destroy(pmp_hbp *hp)
@@ -1502,7 +1549,10 @@ pmp_status pmp_eval_population(pmp_instance *inst, const uint64_t *masks,
         dfit = inst->h_fit;
         dscan = scan_total ? inst->h_scan : nullptr;
     }
-    if (!async)
+    // A waiting call's error bits come back through the reduction; the
+    // per-chromosome scheme has none and clears and copies the error word.
+    const bool folded = !async && scheme != PMP_EVAL_PER_CHROMOSOME;
+    if (!async && !folded)
         HIP_TRY(launch_zero(inst->err, sizeof(uint32_t), s));
 
     EvalArgs a{};
@@ -1512,7 +1562,7 @@ pmp_status pmp_eval_population(pmp_instance *inst, const uint64_t *masks,
     a.P = P;
     a.active = nullptr;
     a.done = nullptr;
-    a.err = inst->err;
+    a.err = folded ? inst->err_now : inst->err;
     // (wide chromosomes take the device-memory tile walk, 16 waves only)
     a.waves = wide ? 16 : eval_waves(inst->n, P, inst->m, inst->p, inst->W);
     a.clients_per_block = clients_per_block(inst->n, P, inst->m, inst->p, inst->W, false, a.waves);
@@ -1556,7 +1606,7 @@ pmp_status pmp_eval_population(pmp_instance *inst, const uint64_t *masks,
         HIP_TRY(launch_eval_per_chromosome(a, dfit, dscan, s));
     } else {
         HIP_TRY(scheme == PMP_EVAL_PER_CLIENT ? launch_eval_per_client(a, s) : launch_eval(a, s));
-        HIP_TRY(launch_reduce(a, dfit, dscan, s));
+        HIP_TRY(launch_reduce(a, dfit, dscan, s, folded ? inst->err_out() : ErrOut{}));
     }
 
     if (!on_dev) {
@@ -1568,6 +1618,10 @@ pmp_status pmp_eval_population(pmp_instance *inst, const uint64_t *masks,
     }
     if (async)
         return PMP_OK;
+    if (folded) {
+        HIP_TRY(hipStreamSynchronize(s));
+        return status_from_err(*inst->host_err);
+    }
     uint32_t herr = 0;
     HIP_TRY(hipMemcpyAsync(&herr, inst->err, sizeof herr, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
@@ -1610,7 +1664,7 @@ pmp_status pmp_eval_population_noalloc(pmp_instance *inst, const uint64_t *masks
     a.P = P;
     a.active = nullptr;
     a.done = nullptr;
-    a.err = inst->err;
+    a.err = async ? inst->err : inst->err_now;
     a.tiles_c = (P + kEvalTile - 1) / kEvalTile;
     a.waves = eval_waves(inst->n, P, inst->m, inst->p, inst->W);
     int64_t cpb = clients_per_block(inst->n, P, inst->m, inst->p, inst->W, false, a.waves);
@@ -1628,17 +1682,13 @@ pmp_status pmp_eval_population_noalloc(pmp_instance *inst, const uint64_t *masks
     a.tiles_i = (int32_t)ti;
     a.part = (unsigned long long *)ws;
     a.spart = scan_total ? (uint32_t *)((unsigned char *)ws + kNoAllocCells * 8) : nullptr;
-    if (!async)
-        HIP_TRY(launch_zero(inst->err, sizeof(uint32_t), s));
     HIP_TRY(launch_eval(a, s));
     HIP_TRY(launch_reduce(a, (unsigned long long *)fitness, (unsigned long long *)scan_total,
-                          s));
+                          s, async ? ErrOut{} : inst->err_out()));
     if (async)
         return PMP_OK;
-    uint32_t herr = 0;
-    HIP_TRY(hipMemcpyAsync(&herr, inst->err, sizeof herr, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    return status_from_err(herr);
+    return status_from_err(*inst->host_err);
 }
 
 void pmp_ga_destroy(pmp_ga *ga)
