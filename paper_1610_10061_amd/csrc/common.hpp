@@ -117,6 +117,10 @@ __device__ __forceinline__ int wave_id()
 constexpr int kMaxPersistentBlocks = 4096;
 constexpr int kBarrierWords = 32 * (kMaxPersistentBlocks + 1);
 
+// Entries allocated past the last row of Pi': a walk may load a chunk that
+// starts past its row (k_eval's walk_rest), without using it.
+constexpr int kRowPad = 192;
+
 constexpr int kEvalTile = 64;     // chromosomes per block (one per lane)
 constexpr int kEvalWaves = 4;     // waves per block
 

@@ -159,36 +159,101 @@ __device__ __forceinline__ void first_open2(uint64_t row, int lane, const Transp
     hit_b = lowest_bit(hi);
 }
 
-// The rest of one client's walk from position `base` for the chromosomes in
-// `pend` (64-entry chunks, loaded here).  sT: the tile's facility-major masks,
-// with an all-zero word at index jz for positions past the row.
-__device__ __forceinline__ void walk_tail(const EvalArgs &a, const uint16_t *prow,
-                                          const int32_t *drow, int base, uint64_t pend,
+// A chunk in which at most this many chromosomes can still find their first
+// open facility is finished one facility at a time (below) instead of by a
+// transpose.
+constexpr int kSerialHits = 4;
+
+// The rest of one client's walk from position `from` for the chromosomes in
+// `pend`, in the row's aligned 64-entry chunks.  sT: the tile's
+// facility-major masks, with an all-zero word at index jz for positions
+// before `from` or past the row.
+//
+// With long scans most chunks serve few chromosomes: at m = 5000, p = 10 a
+// client's walk takes about 33 chunks for its 64 first hits, and past the
+// fifth chunk fewer than 4 of them fall into one chunk, so a transpose per
+// chunk (about 35 VALU instructions whatever it finds) is mostly work for
+// chromosomes that are done.  The positions open in a pending chromosome are
+// found by two ands and a compare; when they or the pending chromosomes are
+// few, the lowest is taken, with the chromosomes it is first for as an exec
+// mask, and the rest is looked at again (about 7 VALU instructions each).
+// Only fuller chunks are transposed.  Only the positions are kept; the
+// distances are gathered once at the end, so that a chunk loads 128 bytes of
+// Pi' and no D'.  The next chunk is in flight meanwhile (rows are padded to
+// whole chunks).  Measured at m = n = 5000, p = 10, 4096 chromosomes: 4.6e8
+// -> 2.4e8 VALU instructions, 0.87 -> 0.535 ms (0.72 of the VALU issue rate
+// and 0.6 of the scalar unit's); the threshold 4 is where 8 instructions a
+// hit meet the transpose's 35.
+//
+// The gathered distances stay in flight: `late` holds the last call's until
+// the next call, or the caller's end, adds them up.
+struct LateCosts {
+    int32_t d = 0;
+    uint32_t keep = 0;  // all ones in the lanes that take d
+
+    __device__ __forceinline__ void add_to(unsigned long long &acc) const
+    {
+        acc += (uint32_t)d & keep;
+    }
+};
+
+__device__ __forceinline__ void walk_rest(const EvalArgs &a, const uint16_t *prow,
+                                          const int32_t *drow, int from, uint64_t pend,
                                           int lane, const uint64_t *sT, uint32_t jz,
                                           const TransposeLanes &tl, unsigned long long &acc,
-                                          uint32_t &scn)
+                                          uint32_t &scn, LateCosts &late)
 {
-    for (; pend != 0ull; base += 64) {
-        if (base >= a.t.K) {  // fewer than p open facilities
-            if (lane == 0)
-                atomicOr(a.err, ERR_SCAN_OVERRUN);
-            break;
+    const int K = a.t.K;
+    int base = from & ~63;
+    uint32_t scan = 0;  // position + 1 of the lane's chromosome, once found
+    // byte offset of the lane's next entry in the row; the chunk past the
+    // row's end that a walk may load (and not use) is still in the table,
+    // which is padded by kRowPad entries
+    uint32_t off = 2u * (uint32_t)(base + lane);
+    const uint32_t off_from = 2u * (uint32_t)from, off_n = 2u * (uint32_t)max(K - from, 0);
+    const char *row_bytes = reinterpret_cast<const char *>(prow);
+    uint32_t j = *reinterpret_cast<const uint16_t *>(row_bytes + off);
+    for (;;) {
+        const uint64_t row = sT[off - off_from < off_n ? j : jz];
+        off += 128u;
+        j = *reinterpret_cast<const uint16_t *>(row_bytes + off);
+        uint64_t hits = __builtin_amdgcn_ballot_w64((row & pend) != 0ull);
+        if (hits != 0ull) {
+            if (min(__builtin_popcountll(hits), __builtin_popcountll(pend)) > kSerialHits) {
+                const int hit = first_open(row, lane, tl);
+                const uint64_t found = pend & __builtin_amdgcn_ballot_w64(hit >= 0);
+                scan = __builtin_amdgcn_inverse_ballot_w64(found) ? (uint32_t)(base + hit + 1)
+                                                                  : scan;
+                pend &= ~found;
+            } else {
+                do {
+                    const int l = __builtin_ctzll(hits);
+                    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)row, l);
+                    const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(row >> 32), l);
+                    const uint64_t fresh = (((uint64_t)hi << 32) | lo) & pend;
+                    scan = __builtin_amdgcn_inverse_ballot_w64(fresh) ? (uint32_t)(base + l + 1)
+                                                                      : scan;
+                    pend &= ~fresh;
+                    hits = __builtin_amdgcn_ballot_w64((row & pend) != 0ull);
+                } while (hits != 0ull);
+            }
+            base += 64;
+            if (pend == 0ull)
+                break;
+        } else {
+            // (no position of a chunk past the row is open, so this is the
+            // only way past its end)
+            base += 64;
+            if (base >= K)
+                break;
         }
-        const int k = base + lane;
-        const bool in = k < a.t.K;
-        const int kc = in ? k : a.t.K - 1;
-        const uint32_t j = prow[kc];
-        const int32_t dist = drow[kc];
-        const int hit = first_open(sT[in ? j : jz], lane, tl);
-        const bool found = ((pend >> lane) & 1ull) && hit >= 0;
-        const int32_t cost = __builtin_amdgcn_ds_bpermute(hit << 2, dist);
-        if (found) {
-            acc += (uint32_t)cost;
-            scn += (uint32_t)(base + hit + 1);
-        }
-        // (= pend & ~ballot(found): found is hit >= 0 on pend's lanes)
-        pend &= ~__builtin_amdgcn_ballot_w64(hit >= 0);
     }
+    if (pend != 0ull && lane == 0)  // fewer than p open facilities
+        atomicOr(a.err, ERR_SCAN_OVERRUN);
+    late.add_to(acc);
+    late.d = drow[max(scan, 1u) - 1u];
+    late.keep = scan != 0u ? ~0u : 0u;
+    scn += scan;
 }
 
 // LDS words (32-bit) eval_tile needs for its staged masks: rows of WD words
@@ -217,7 +282,7 @@ constexpr int eval_stage_words()
 //
 // H (short scans, not with R): a wave walks its clients two at a time, the
 // first 32 entries of each row in one chunk (first_open2); the few rows
-// whose first open facility lies past entry 31 finish in walk_tail.
+// whose first open facility lies past entry 31 finish in walk_rest.
 //
 // PRE: the caller has already staged the tile's masks in smask (rows at
 // stride WD + 1, zero past 2W words) and the chromosomes' active flags in
@@ -446,6 +511,7 @@ __device__ __forceinline__ void eval_tile(const EvalArgs &a, int ti, int tc,
     }
     unsigned long long acc = 0;
     uint32_t scn = 0;
+    LateCosts late;
     if constexpr (H) {
         for (; i < i1; i += 2 * NV) {
             const int ib = i + NV;
@@ -473,11 +539,11 @@ __device__ __forceinline__ void eval_tile(const EvalArgs &a, int ti, int tc,
             const uint64_t ra = pa & ~__builtin_amdgcn_ballot_w64(ha >= 0);
             const uint64_t rb = pb & ~__builtin_amdgcn_ballot_w64(hb >= 0);
             if (ra)
-                walk_tail(a, a.t.pi + (int64_t)i * a.t.pitch, a.t.ds + (int64_t)i * a.t.pitch,
-                          32, ra, lane, sT, jz, tl, acc, scn);
+                walk_rest(a, a.t.pi + (int64_t)i * a.t.pitch, a.t.ds + (int64_t)i * a.t.pitch,
+                          32, ra, lane, sT, jz, tl, acc, scn, late);
             if (rb)
-                walk_tail(a, a.t.pi + (int64_t)ib * a.t.pitch, a.t.ds + (int64_t)ib * a.t.pitch,
-                          32, rb, lane, sT, jz, tl, acc, scn);
+                walk_rest(a, a.t.pi + (int64_t)ib * a.t.pitch, a.t.ds + (int64_t)ib * a.t.pitch,
+                          32, rb, lane, sT, jz, tl, acc, scn, late);
             j_cur = j_nxt;
             d_cur = d_nxt;
         }
@@ -505,7 +571,21 @@ __device__ __forceinline__ void eval_tile(const EvalArgs &a, int ti, int tc,
         const int32_t *drow = a.t.ds + (int64_t)i * a.t.pitch;
         const long long *erow = R ? a.e64 + (int64_t)i * a.t.pitch : nullptr;
         uint64_t pend = act;
-        for (int base = 0; pend != 0ull; base += 64) {
+        if constexpr (!R) {
+            // the first chunk (by a transpose: most chromosomes stop in it),
+            // the others in walk_rest
+            const int hit = first_open(sT[in_row ? j_cur : jz], lane, tl);
+            const bool found = ((pend >> lane) & 1ull) && hit >= 0;
+            const int32_t cost = __builtin_amdgcn_ds_bpermute(hit << 2, d_cur);
+            if (found) {
+                acc += (uint32_t)cost;
+                scn += (uint32_t)(hit + 1);
+            }
+            pend &= ~__builtin_amdgcn_ballot_w64(hit >= 0);  // as in walk_rest
+            if (pend != 0ull)
+                walk_rest(a, prow, drow, 64, pend, lane, sT, jz, tl, acc, scn, late);
+        }
+        for (int base = 0; R && pend != 0ull; base += 64) {
             if (base >= a.t.K) {  // fewer than p open facilities
                 if (lane == 0)
                     atomicOr(a.err, ERR_SCAN_OVERRUN);
@@ -514,50 +594,36 @@ __device__ __forceinline__ void eval_tile(const EvalArgs &a, int ti, int tc,
             const int k = base + lane;
             uint32_t j = 0;
             bool use = false;
-            int32_t dist = 0;
             long long ev = 0;
             if (base == 0) {
                 j = j_cur;
                 use = in_row;
-                if (R)
-                    ev = e_cur;
-                else
-                    dist = d_cur;
+                ev = e_cur;
             } else if (k < a.t.K) {
                 j = prow[k];
                 use = true;
-                if (R)
-                    ev = erow[k];
-                else
-                    dist = drow[k];
+                ev = erow[k];
             }
             uint32_t jt = use ? j : jz;
-            if (R && k == k_cur - 1)  // the row's last kept position
+            if (k == k_cur - 1)  // the row's last kept position
                 jt = jone;
             const int hit = first_open(sT[jt], lane, tl);
             const bool found = ((pend >> lane) & 1ull) && hit >= 0;
-            if (R) {
-                const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(
-                    hit << 2, (int)(uint32_t)(unsigned long long)ev);
-                const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(
-                    hit << 2, (int)(uint32_t)((unsigned long long)ev >> 32));
-                if (found) {
-                    acc += ((unsigned long long)hi << 32) | lo;
-                    scn += (uint32_t)(base + hit + 1);
-                }
-            } else {
-                const int32_t cost = __builtin_amdgcn_ds_bpermute(hit << 2, dist);
-                if (found) {
-                    acc += (uint32_t)cost;
-                    scn += (uint32_t)(base + hit + 1);
-                }
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(
+                hit << 2, (int)(uint32_t)(unsigned long long)ev);
+            const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(
+                hit << 2, (int)(uint32_t)((unsigned long long)ev >> 32));
+            if (found) {
+                acc += ((unsigned long long)hi << 32) | lo;
+                scn += (uint32_t)(base + hit + 1);
             }
-            pend &= ~__builtin_amdgcn_ballot_w64(hit >= 0);  // as in walk_tail
+            pend &= ~__builtin_amdgcn_ballot_w64(hit >= 0);  // as in walk_rest
         }
         e_cur = e_nxt;
         k_cur = k_nxt;
     }
 
+    late.add_to(acc);
     sred[wave * kEvalTile + lane] = acc;
     sred[NV * kEvalTile + wave * kEvalTile + lane] = scn;
     __syncthreads();

@@ -511,9 +511,12 @@ __global__ __launch_bounds__(64 * kGaWaves) void k_batch_init(BatchArgs B)
 // fastest shape of the single-run evaluation too).
 constexpr int kBatchEvalWaves = 16;
 
+// (At most 80 SGPRs: above that a SIMD holds 7 waves, so one workgroup of 16
+// fits a CU instead of two; with 82 a launch took 3.6 M instead of 2.5 M busy
+// cycles for fewer instructions.)
 template <int WD>
-__global__ __launch_bounds__(kEvalTile *kBatchEvalWaves) void k_batch_eval(BatchArgs B, int k,
-                                                                           int buf)
+__global__ __launch_bounds__(kEvalTile *kBatchEvalWaves)
+    __attribute__((amdgpu_num_sgpr(80))) void k_batch_eval(BatchArgs B, int k, int buf)
 {
     __shared__ __align__(16) uint32_t smask[eval_stage_words<WD>()];
     __shared__ unsigned long long sred[2 * kBatchEvalWaves * kEvalTile];

@@ -1009,7 +1009,7 @@ pmp_status pmp_preprocess(const int32_t *d, int64_t ld, int32_t n, int32_t m,
     inst->pitch = ((inst->K + 63) / 64) * 64;
     const size_t cells = (size_t)n * inst->pitch;
     inst->near_len = (m + p - 1) / p;
-    inst->arena.add(&inst->pi, cells);
+    inst->arena.add(&inst->pi, cells + kRowPad);
     inst->arena.add(&inst->ds, cells);
     inst->arena.add(&inst->delta, cells);
     inst->arena.add(&inst->err, 64);
