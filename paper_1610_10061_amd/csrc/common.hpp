@@ -114,6 +114,27 @@ __device__ __forceinline__ int wave_id()
     return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 }
 
+// Wave-wide inclusive prefix sums with DPP lane moves instead of LDS
+// permutes: shifts by 1, 2, 4 and 8 within each 16-lane row (lanes without
+// a source add 0), then the last lane of row 0 and of row 2 is broadcast into
+// rows 1 and 3, and the last lane of row 1 into rows 2 and 3.
+template <int Ctrl, int RowMask>
+__device__ __forceinline__ uint32_t dpp_from(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, Ctrl, RowMask, 0xF, false);
+}
+
+__device__ __forceinline__ uint32_t wave_scan_incl(uint32_t v, int /*lane*/)
+{
+    v += dpp_from<0x111, 0xF>(v);  // row_shr:1
+    v += dpp_from<0x112, 0xF>(v);  // row_shr:2
+    v += dpp_from<0x114, 0xF>(v);  // row_shr:4
+    v += dpp_from<0x118, 0xF>(v);  // row_shr:8
+    v += dpp_from<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+    v += dpp_from<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
 constexpr int kMaxPersistentBlocks = 4096;
 constexpr int kBarrierWords = 32 * (kMaxPersistentBlocks + 1);
 
@@ -123,6 +144,9 @@ constexpr int kRowPad = 192;
 
 constexpr int kEvalTile = 64;     // chromosomes per block (one per lane)
 constexpr int kEvalWaves = 4;     // waves per block
+
+// Widest row that one workgroup sorts in LDS (k_preprocess.hip).
+constexpr int kMaxLdsRow = 23552;
 
 // Launchers (each lives with its kernels).
 hipError_t launch_sort_rows(const int32_t *d, int64_t ld, int32_t n, int32_t m,
@@ -147,7 +171,7 @@ hipError_t launch_reduce(const EvalArgs &a, unsigned long long *fitness,
 // chromosomes, a.t.W words each) and the feasibility check of every
 // chromosome (error bits into a.err).
 hipError_t launch_tile_major(const EvalArgs &a, uint64_t *tg, hipStream_t s);
-// Rows wider than PMP_MAX_FACILITIES: the sort in device memory, `batch`
+// Rows wider than kMaxLdsRow: the sort in device memory, `batch`
 // rows at a time in `scratch` (batch x m2 keys, m2 = m rounded up to a power
 // of two).
 int wide_sort_rows_per_batch(int32_t m);

@@ -43,28 +43,8 @@ __device__ __forceinline__ int ga_xstages(const GaArgs &g)
     return (g.t.p >= 2 && g.lg > 0) ? g.X : 0;
 }
 
-// Wave-wide inclusive prefix sums with DPP lane moves instead of LDS
-// permutes: shifts by 1, 2, 4 and 8 within each 16-lane row (lanes without
-// a source add 0), then the last lane of row 0 and of row 2 is broadcast into
-// rows 1 and 3, and the last lane of row 1 into rows 2 and 3.
-template <int Ctrl, int RowMask>
-__device__ __forceinline__ uint32_t dpp_from(uint32_t v)
-{
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, Ctrl, RowMask, 0xF, false);
-}
-
-__device__ __forceinline__ uint32_t wave_scan_incl(uint32_t v, int /*lane*/)
-{
-    v += dpp_from<0x111, 0xF>(v);  // row_shr:1
-    v += dpp_from<0x112, 0xF>(v);  // row_shr:2
-    v += dpp_from<0x114, 0xF>(v);  // row_shr:4
-    v += dpp_from<0x118, 0xF>(v);  // row_shr:8
-    v += dpp_from<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
-    v += dpp_from<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
-    return v;
-}
-
-// The same on 64-bit values (low and high words, carry by compare).
+// One step of wave_scan_incl on 64-bit values (low and high words, carry by
+// compare).
 template <int Ctrl, int RowMask>
 __device__ __forceinline__ void dpp_add64(uint32_t &lo, uint32_t &hi)
 {

@@ -3,15 +3,10 @@
 // entries of the ordering Pi', the gap terms Delta' and the sorted distances
 // D'.
 //
-// One workgroup sorts one row in LDS.  A facility becomes the key
-// (d_ij << 16) | j; keys are distinct, so an ascending sort of keys is the
-// order by distance with ties broken by the lower index, the order the
-// paper's Example 1 prints.  When every distance of the row is below 2^16
-// the key fits 32 bits, so the sort moves half the LDS bytes and twice as
-// many rows are sorted at once; otherwise it takes 64 bits.  The row is padded to a power of two with all-ones keys
-// and sorted by a bitonic network (Batcher, 1968).  The epilogue splits the
-// first K keys back into index and distance and takes the first difference
-// of the distances.
+// One workgroup sorts one row in LDS by a stable least-significant-digit
+// radix sort of the distances (Knuth, TAOCP 3, 5.2.5).  The facilities enter
+// in index order, so stability alone breaks ties by the lower index, the
+// order the paper's Example 1 prints.
 #include <algorithm>
 
 #include "common.hpp"
@@ -20,108 +15,277 @@ namespace pmp {
 
 namespace {
 
-constexpr int kSortThreads = 512;
-constexpr int kSortPerThread = PMP_MAX_FACILITIES / kSortThreads;  // 16
+constexpr int kSortThreads = 512;  // workgroups of the device-memory sort below
 
-// Compare-exchange t of a stage joins keys lo = 2t - (t mod stride) and
-// lo + stride.  With stride <= 32 the 64 threads of a wave (t in an aligned
-// block of 64) touch only their own aligned block of 128 keys, the same
-// block in every such stage, so consecutive stages of that kind need only
-// the wave's own ordering; a workgroup barrier is needed around the others.
-template <class Key>
-__device__ __forceinline__ void bitonic_sort(Key *key, int m2)
+// ---------------------------------------------------------------------------
+// k_radix_rows: a workgroup of NW waves sorts a row of up to NW I 64
+// facilities, wave w holding the I vectors of 64 consecutive facilities from
+// w I on in registers.
+//
+// The row's widest distance (an OR over the row) gives the bits to sort by
+// and so the passes: ceil(bits / 8) of bits / passes bits each, 6 at least
+// (graph distances below 2^8 take one, a 10^4 grid's two, rows of zeros none).
+// A pass counts and ranks: for each of its vectors in order a wave finds the
+// lanes with the same digit by a ballot per digit bit, a lane's rank is the
+// wave's count of the digit so far plus the equal lanes below it, and the
+// lowest of the equal lanes adds their number to the count (a wave's LDS
+// accesses execute in order, so the vectors pipeline without waits).  Two
+// waves share a 32-bit word of counts, 16 bits each.  An exclusive sum over
+// (digit, wave) then gives every wave's first place of each digit, and the
+// keys are scattered to their places in LDS.
+//
+// While every distance is below 2^16 a key is distance << 16 | facility, one
+// LDS word; otherwise distances and facilities are scattered to two arrays.
+//
+// Bound: a vector costs about 4 VALU instructions per digit bit and 20 per
+// pass, and the waves wait at four barriers a pass.  A bitonic network in LDS
+// (91 compare-exchange stages at m = 5000) took 792 us for 5000 rows of
+// 14-bit distances, moving every key through LDS in every stage; this sort
+// takes 121 us (350 MB of rows and tables: 2.9 TB/s), 178 us with 21-bit
+// distances.  900 rows of 900 (one pass): 37 -> 7 us; 777 rows of 20001 with
+// 21 bits: 1.28 ms in device memory -> 0.19 ms.  Shapes (waves, vectors per
+// wave) follow m so that at most a few vectors are padding: rows up to 8192
+// keep two or more workgroups per CU (16 waves of 5 vectors instead of 8 of
+// 10 leave one: 182 us), wider ones take one workgroup of 16 waves and its
+// CU's LDS, 6 bytes a facility.
+// ---------------------------------------------------------------------------
+constexpr int kDigits = 256;
+
+template <int NW>
+constexpr int count_words()  // one set of counts: two waves to a word
 {
-    const int half = m2 >> 1;
-    for (int size = 2; size <= m2; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int t = threadIdx.x; t < half; t += kSortThreads) {
-                const int lo = 2 * t - (t & (stride - 1));
-                const int hi = lo + stride;
-                const bool ascending = (lo & size) == 0;
-                const Key a = key[lo], b = key[hi];
-                if ((a > b) == ascending) {
-                    key[lo] = b;
-                    key[hi] = a;
-                }
+    return NW / 2 * kDigits;
+}
+
+// Counts and ranks of one pass (DB digit bits from bit sh of the keys): a
+// wave's counts go to its half of the words `mine`, each key's place among
+// the wave's keys of its digit to the low half of rank.
+template <int DB, int I, bool NARROW>
+__device__ __forceinline__ void radix_count(const uint32_t (&key)[I], uint32_t (&rank)[I], int sh,
+                                            uint32_t *mine, int half)
+{
+#pragma unroll
+    for (int r = 0; r < I; ++r) {
+        const uint32_t d = (key[r] >> sh) & (uint32_t)((1 << DB) - 1);
+        uint32_t lo = 0u, hi = 0u;  // lanes with another digit
+#pragma unroll
+        for (int b = 0; b < DB; ++b) {
+            const uint32_t t = (uint32_t)__builtin_amdgcn_sbfe((int)d, b, 1);  // 0 or all ones
+            const uint64_t ones = __builtin_amdgcn_ballot_w64(t != 0u);
+            lo |= (uint32_t)ones ^ t;
+            hi |= (uint32_t)(ones >> 32) ^ t;
+        }
+        const uint32_t below = __builtin_amdgcn_mbcnt_hi(~hi, __builtin_amdgcn_mbcnt_lo(~lo, 0u));
+        // every lane reads before the lowest lane of each digit adds
+        const uint32_t before =
+            __hip_atomic_load(mine + d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (below == 0u)
+            __hip_atomic_fetch_add(mine + d,
+                                   (uint32_t)(64 - __builtin_popcount(lo) - __builtin_popcount(hi))
+                                       << half,
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        const uint32_t place = ((before >> half) & 0xFFFFu) + below;
+        rank[r] = NARROW ? place : (rank[r] & 0xFFFF0000u) | place;
+    }
+}
+
+template <int NW, int I, bool NARROW>
+__device__ __forceinline__ void radix_sort_row(uint32_t (&key)[I], int bits, uint32_t *counts,
+                                               uint32_t *wave_total, uint32_t *keys,
+                                               uint16_t *idx)
+{
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    const int first = wave * I * 64 + lane;
+    // digits of 6, 7 or 8 bits (two waves: at most 7, a digit per thread)
+    constexpr int kMost = NW >= 4 ? 8 : 7;
+    const int passes = (bits + kMost - 1) / kMost;
+    const int db = passes ? max(6, (bits + passes - 1) / passes) : 0;
+    // low half: the rank in a pass; high half: the facility (not NARROW)
+    uint32_t rank[I];
+#pragma unroll
+    for (int r = 0; r < I; ++r)
+        rank[r] = NARROW ? 0u : (uint32_t)(first + 64 * r) << 16;
+    if (passes == 0) {  // all distances zero: index order
+#pragma unroll
+        for (int r = 0; r < I; ++r) {
+            keys[first + 64 * r] = key[r];
+            if constexpr (!NARROW)
+                idx[first + 64 * r] = (uint16_t)(rank[r] >> 16);
+        }
+    }
+    const int ndig = 1 << db, half = (wave & 1) * 16;
+    for (int p = 0; p < passes; ++p) {
+        const int sh = p * db + (NARROW ? 16 : 0);
+        uint32_t *cnt = counts + (p & 1) * count_words<NW>();
+        uint32_t *spare = counts + ((p & 1) ^ 1) * count_words<NW>();
+        uint32_t *mine = cnt + (wave >> 1) * kDigits;
+        if (db == 6)
+            radix_count<6, I, NARROW>(key, rank, sh, mine, half);
+        else if (db == 7)
+            radix_count<7, I, NARROW>(key, rank, sh, mine, half);
+        else if constexpr (kMost == 8)
+            radix_count<8, I, NARROW>(key, rank, sh, mine, half);
+        __syncthreads();
+        // counts -> first places: over the waves of a digit, then the digits
+        const int t = (int)threadIdx.x;
+        uint32_t at[NW / 2];
+        uint32_t sum = 0;
+        if (t < ndig) {
+#pragma unroll
+            for (int q = 0; q < NW / 2; ++q) {
+                const uint32_t c = cnt[q * kDigits + t];
+                at[q] = sum | ((sum + (c & 0xFFFFu)) << 16);
+                sum += (c & 0xFFFFu) + (c >> 16);
             }
-            const int next = stride > 1 ? stride >> 1 : size;  // the next stage's stride
-            if (stride > 32 || next > 32) {
-                __syncthreads();
-            } else {
-                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                __builtin_amdgcn_wave_barrier();
+        }
+        const uint32_t incl = wave_scan_incl(sum, lane);
+        if (lane == 63)
+            wave_total[wave] = incl;
+        for (int k = t; k < count_words<NW>(); k += 64 * NW)
+            spare[k] = 0u;  // the next pass's counts
+        __syncthreads();
+        if (t < ndig) {
+            uint32_t base = incl - sum;
+#pragma unroll
+            for (int v = 0; v < kDigits / 64 - 1; ++v)
+                base += v < wave ? wave_total[min(v, NW - 1)] : 0u;
+#pragma unroll
+            for (int q = 0; q < NW / 2; ++q)
+                cnt[q * kDigits + t] = at[q] + base * 0x10001u;
+        }
+        __syncthreads();
+        // (digits are taken from the keys again: kept, they and their
+        // addresses would cost 2 I registers)
+#pragma unroll
+        for (int r = 0; r < I; ++r)
+            asm volatile("" : "+v"(key[r]));
+#pragma unroll
+        for (int r = 0; r < I; ++r) {
+            const uint32_t d = (key[r] >> sh) & (uint32_t)(ndig - 1);
+            const uint32_t o = ((mine[d] >> half) & 0xFFFFu) + (rank[r] & 0xFFFFu);
+            keys[o] = key[r];
+            if constexpr (!NARROW)
+                idx[o] = (uint16_t)(rank[r] >> 16);
+        }
+        if (p + 1 < passes) {
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < I; ++r) {
+                key[r] = keys[first + 64 * r];
+                if constexpr (!NARROW)
+                    rank[r] = (uint32_t)idx[first + 64 * r] << 16;
             }
         }
     }
     __syncthreads();
 }
 
-template <class Key>
-__device__ __forceinline__ void emit_row(const Key *key, int K, int pitch, int64_t base,
-                                         uint16_t *pi, int32_t *delta, int32_t *ds)
+// The first K sorted entries, four per thread (a row of the tables starts on
+// a multiple of 64 entries), zeros up to the pitch.
+template <int NW, bool NARROW>
+__device__ __forceinline__ void emit_sorted(const uint32_t *keys, const uint16_t *idx, int K,
+                                            int pitch, int64_t base, uint16_t *pi,
+                                            int32_t *delta, int32_t *ds)
 {
-    for (int k = threadIdx.x; k < pitch; k += kSortThreads) {
-        uint16_t f = 0;
-        int32_t dist = 0, gap = 0;
-        if (k < K) {
-            const Key x = key[k];
-            f = (uint16_t)(x & 0xFFFFu);
-            dist = (int32_t)(x >> 16);
-            gap = k == 0 ? dist : dist - (int32_t)(key[k - 1] >> 16);
+    for (int k = 4 * (int)threadIdx.x; k < pitch; k += 4 * 64 * NW) {
+        const uint4 q = *reinterpret_cast<const uint4 *>(keys + k);
+        const uint32_t x[5] = {k ? keys[k - 1] : 0u, q.x, q.y, q.z, q.w};
+        ushort4 j = NARROW ? make_ushort4((uint16_t)q.x, (uint16_t)q.y, (uint16_t)q.z,
+                                          (uint16_t)q.w)
+                           : *reinterpret_cast<const ushort4 *>(idx + k);
+        int32_t dist[5];
+#pragma unroll
+        for (int c = 0; c < 5; ++c)
+            dist[c] = (int32_t)(NARROW ? x[c] >> 16 : x[c]);
+        if (k + 4 > K) {  // the row's end
+            j.x = k < K ? j.x : 0;
+            j.y = k + 1 < K ? j.y : 0;
+            j.z = k + 2 < K ? j.z : 0;
+            j.w = 0;
         }
-        pi[base + k] = f;
-        ds[base + k] = dist;
-        delta[base + k] = gap;
+        int32_t v[4], g[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            v[c] = k + c < K ? dist[c + 1] : 0;
+            g[c] = k + c < K ? dist[c + 1] - dist[c] : 0;
+        }
+        *reinterpret_cast<ushort4 *>(pi + base + k) = j;
+        *reinterpret_cast<int4 *>(ds + base + k) = make_int4(v[0], v[1], v[2], v[3]);
+        *reinterpret_cast<int4 *>(delta + base + k) = make_int4(g[0], g[1], g[2], g[3]);
     }
 }
 
-// Two launches, one per key width: the 32-bit one (m2 x 4 bytes of LDS, so
-// twice as many workgroups stay resident) sorts the rows whose distances are
-// all below 2^16 and checks every row for negative distances; the 64-bit one
-// sorts the others.  Each reads the row and skips it when it belongs to the
-// other.  m2 <= PMP_MAX_FACILITIES; dynamic LDS holds m2 keys.
-template <class Key>
-__global__ __launch_bounds__(kSortThreads) void k_sort_rows(
-    const int32_t *__restrict__ d, int64_t ld, int32_t m, int32_t m2,
-    int32_t K, int32_t pitch, uint16_t *__restrict__ pi,
-    int32_t *__restrict__ delta, int32_t *__restrict__ ds,
-    uint32_t *__restrict__ err)
+// Waves per SIMD the registers are held to.  More waves hide the barriers and
+// the LDS round trips better than a few spilled values cost (4801 rows of
+// 3333: 95 us at 6, 92 at 8; 5000 of 5000: 129 at 5, 121 at 6).
+constexpr int radix_waves_per_simd(int NW, int I)
 {
-    constexpr bool k32 = sizeof(Key) == 4;
-    extern __shared__ uint64_t lds_keys[];
-    Key *key = reinterpret_cast<Key *>(lds_keys);
-    const int32_t i = blockIdx.x;
-    const int32_t *row = d + (int64_t)i * ld;
-    int32_t v[kSortPerThread];
-    int negative = 0, wide = 0;
+    return NW == 16 ? 4 : I <= 8 ? 8 : I <= 12 ? 6 : 4;
+}
+
+template <int NW, int I>
+__global__ __launch_bounds__(64 * NW, radix_waves_per_simd(NW, I)) void k_radix_rows(const int32_t *__restrict__ d, int64_t ld,
+                                                        int32_t m, int32_t K, int32_t pitch,
+                                                        uint16_t *__restrict__ pi,
+                                                        int32_t *__restrict__ delta,
+                                                        int32_t *__restrict__ ds,
+                                                        uint32_t *__restrict__ err)
+{
+    extern __shared__ __align__(16) uint32_t lds_words[];
+    __shared__ uint32_t wave_word[NW];
+    uint32_t *counts = lds_words;                        // two sets
+    uint32_t *keys = lds_words + 2 * count_words<NW>();  // NW I 64
+    uint16_t *idx = reinterpret_cast<uint16_t *>(keys + NW * I * 64);
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    const int64_t i = blockIdx.x;
+    const int32_t *row = d + i * ld;
+    uint32_t key[I];
 #pragma unroll
-    for (int r = 0; r < kSortPerThread; ++r) {
-        const int j = threadIdx.x + r * kSortThreads;
-        v[r] = row[j < m ? j : m - 1];  // every load at a valid address
-        if (j < m) {
-            negative |= v[r] < 0;
-            wide |= v[r] >= 65536;
-        }
-    }
-    if (k32 && __syncthreads_or(negative) && threadIdx.x == 0)
+    for (int r = 0; r < I; ++r)  // every load at a valid address
+        key[r] = (uint32_t)row[min((wave * I + r) * 64 + lane, m - 1)];
+    for (int k = (int)threadIdx.x; k < 2 * count_words<NW>(); k += 64 * NW)
+        counts[k] = 0u;
+    uint32_t any = 0;
+#pragma unroll
+    for (int r = 0; r < I; ++r)
+        any |= key[r];  // (a clamped load repeats a distance of the row)
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+        any |= (uint32_t)__shfl_xor((int)any, o);
+    if (lane == 0)
+        wave_word[wave] = any;
+    __syncthreads();
+    any = 0;
+#pragma unroll
+    for (int v = 0; v < NW; ++v)
+        any |= wave_word[v];
+    any = __builtin_amdgcn_readfirstlane(any);
+    __syncthreads();  // (wave_word is used again)
+    const int bits = any ? 32 - __builtin_clz(any) : 0;
+    if ((int32_t)any < 0 && threadIdx.x == 0)
         atomicOr(err, ERR_NEGATIVE_DISTANCE);
-    if ((__syncthreads_or(wide) != 0) == k32)
-        return;  // the other launch's row
+    // padding past m: the last keys of every pass's last digit
+    if (bits <= 16) {
 #pragma unroll
-    for (int r = 0; r < kSortPerThread; ++r) {
-        const int j = threadIdx.x + r * kSortThreads;
-        if (j < m2)
-            key[j] = j < m ? ((Key)(uint32_t)v[r] << 16) | (Key)j : ~(Key)0;
+        for (int r = 0; r < I; ++r) {
+            const int j = (wave * I + r) * 64 + lane;
+            key[r] = j < m ? (key[r] << 16) | (uint32_t)j : ~0u;
+        }
+        radix_sort_row<NW, I, true>(key, bits, counts, wave_word, keys, idx);
+        emit_sorted<NW, true>(keys, idx, K, pitch, i * pitch, pi, delta, ds);
+    } else {
+#pragma unroll
+        for (int r = 0; r < I; ++r)
+            key[r] = (wave * I + r) * 64 + lane < m ? key[r] : ~0u;
+        radix_sort_row<NW, I, false>(key, bits, counts, wave_word, keys, idx);
+        emit_sorted<NW, false>(keys, idx, K, pitch, i * pitch, pi, delta, ds);
     }
-    __syncthreads();
-    bitonic_sort(key, m2);
-    emit_row(key, K, pitch, (int64_t)i * pitch, pi, delta, ds);
 }
 
 // ---------------------------------------------------------------------------
-// Rows wider than PMP_MAX_FACILITIES (m up to 65535): the same bitonic
-// network on the padded row (m2 keys, a power of two), 64-bit keys, run in
-// device memory.  Each row's keys live in a scratch array; chunks of
+// Rows wider than kMaxLdsRow (m up to 65535): a bitonic network (Batcher,
+// 1968) on the padded row (m2 64-bit keys distance << 16 | facility, a power
+// of two of them), run in device memory.  Each row's keys live in a scratch array; chunks of
 // kWideChunk keys are sorted in LDS by every stage of size <= kWideChunk
 // (compare directions from the keys' global indices, as in the whole
 // network); each larger size runs its strides >= kWideChunk as passes over
@@ -311,21 +475,64 @@ hipError_t launch_sort_rows_wide(const int32_t *d, int64_t ld, int32_t n, int32_
     return hipSuccess;
 }
 
+namespace {
+
+template <int NW, int I>
+hipError_t launch_radix(const int32_t *d, int64_t ld, int32_t n, int32_t m, int32_t K,
+                        int32_t pitch, uint16_t *pi, int32_t *delta, int32_t *ds, uint32_t *err,
+                        hipStream_t s)
+{
+    static_assert(NW * I * 64 <= 65535, "places are counted in 16 bits");
+    const size_t lds = sizeof(uint32_t) * 2 * count_words<NW>() + 6 * (size_t)(NW * I * 64);
+    static_assert(sizeof(uint32_t) * 2 * NW / 2 * kDigits + 6 * NW * I * 64 + 4 * NW <= 163840,
+                  "more than a CU's LDS");
+    if (lds > 65536) {
+        const hipError_t e =
+            hipFuncSetAttribute(reinterpret_cast<const void *>(k_radix_rows<NW, I>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess)
+            return e;
+    }
+    hipLaunchKernelGGL((k_radix_rows<NW, I>), dim3(n), dim3(64 * NW), lds, s, d, ld, m, K, pitch,
+                       pi, delta, ds, err);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+// m <= kMaxLdsRow.
 hipError_t launch_sort_rows(const int32_t *d, int64_t ld, int32_t n, int32_t m,
                             int32_t K, int32_t pitch, uint16_t *pi,
                             int32_t *delta, int32_t *ds, uint32_t *err,
                             hipStream_t s)
 {
-    int32_t m2 = 2;
-    while (m2 < m)
-        m2 <<= 1;
-    hipLaunchKernelGGL(k_sort_rows<uint32_t>, dim3(n), dim3(kSortThreads),
-                       sizeof(uint32_t) * (size_t)m2, s, d, ld, m, m2, K, pitch, pi, delta, ds,
-                       err);
-    hipLaunchKernelGGL(k_sort_rows<uint64_t>, dim3(n), dim3(kSortThreads),
-                       sizeof(uint64_t) * (size_t)m2, s, d, ld, m, m2, K, pitch, pi, delta, ds,
-                       err);
-    return hipGetLastError();
+#define PMP_RADIX(NW, I)                                                                \
+    if (m <= NW * I * 64)                                                               \
+        return launch_radix<NW, I>(d, ld, n, m, K, pitch, pi, delta, ds, err, s);
+    PMP_RADIX(2, 1)
+    PMP_RADIX(2, 2)
+    PMP_RADIX(4, 2)
+    PMP_RADIX(4, 3)
+    PMP_RADIX(4, 4)
+    PMP_RADIX(4, 6)
+    PMP_RADIX(4, 8)
+    PMP_RADIX(8, 5)
+    PMP_RADIX(8, 6)
+    PMP_RADIX(8, 8)
+    PMP_RADIX(8, 10)
+    PMP_RADIX(8, 12)
+    PMP_RADIX(8, 14)
+    PMP_RADIX(8, 16)
+    PMP_RADIX(16, 10)
+    PMP_RADIX(16, 12)
+    PMP_RADIX(16, 14)
+    PMP_RADIX(16, 16)
+    PMP_RADIX(16, 18)
+    PMP_RADIX(16, 20)
+    PMP_RADIX(16, 23)
+#undef PMP_RADIX
+    static_assert(kMaxLdsRow == 16 * 23 * 64, "the widest shape above");
+    return hipErrorInvalidValue;
 }
 
 // Zero a device buffer with a kernel (safe inside stream capture).

@@ -1027,7 +1027,7 @@ pmp_status pmp_preprocess(const int32_t *d, int64_t ld, int32_t n, int32_t m,
         return fail(PMP_ENOMEM, "pinned host memory");
     }
     int32_t *dd = nullptr;
-    uint64_t *wide = nullptr;  // sort scratch of rows wider than PMP_MAX_FACILITIES
+    uint64_t *wide = nullptr;  // sort scratch of rows wider than kMaxLdsRow
     const int32_t *src = d;
     int64_t src_ld = ld;
     pmp_status st = PMP_OK;
@@ -1051,7 +1051,7 @@ pmp_status pmp_preprocess(const int32_t *d, int64_t ld, int32_t n, int32_t m,
             src = dd;
             src_ld = m;
         }
-        if (m <= PMP_MAX_FACILITIES) {
+        if (m <= kMaxLdsRow) {
             e = launch_sort_rows(src, src_ld, n, m, inst->K, inst->pitch, inst->pi,
                                  inst->delta, inst->ds, inst->err, s);
         } else {  // rows wider than one workgroup's LDS: the sort in device memory
