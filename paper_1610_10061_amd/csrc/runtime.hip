@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "device_pool.hpp"
 #include "learn_device.hpp"
 
 using namespace pmp;
@@ -52,14 +53,13 @@ hipError_t dalloc(T **p, size_t count)
     *p = nullptr;
     if (count == 0)
         count = 1;
-    return hipMalloc((void **)p, sizeof(T) * count);
+    return DevicePool::get().alloc((void **)p, sizeof(T) * count);
 }
 
 template <class T>
 void dfree(T *&p)
 {
-    if (p)
-        (void)hipFree((void *)p);
+    DevicePool::get().free((void *)p);
     p = nullptr;
 }
 
@@ -148,7 +148,7 @@ HostWords &host_words()
 }
 
 // Fixed-size buffers of one object carved out of a single device
-// allocation (one hipMalloc and one hipFree instead of one per buffer).
+// block of the device pool (one allocation instead of one per buffer).
 // Members are listed with add(), then carve() allocates and assigns them;
 // release() frees the block and clears the members.  Buffers that are
 // reallocated later keep allocations of their own.
@@ -172,7 +172,7 @@ struct Arena {
     hipError_t carve()
     {
         const size_t total = bytes();
-        hipError_t e = hipMalloc(&base, total);
+        hipError_t e = DevicePool::get().alloc(&base, total);
         if (e != hipSuccess) {
             base = nullptr;
             return e;
@@ -190,8 +190,7 @@ struct Arena {
     {
         for (const auto &m : members)
             *m.first = nullptr;
-        if (base)
-            (void)hipFree(base);
+        DevicePool::get().free(base);
         base = nullptr;
         members.clear();
     }
@@ -446,6 +445,7 @@ struct BatchHost {
 
     void release()
     {
+        DevicePool::FreeScope frees;
         drop_graphs();
         dfree(d_items);
         dfree(d_prefix);
@@ -726,8 +726,7 @@ struct pmp_ga {
         dfree(cand);
         dfree(cbits);
         dfree(cpre);
-        if (sums)
-            (void)hipFree(sums);
+        DevicePool::get().free(sums);
         sums = nullptr;
         dfree(last_trained);
         dfree(s12);
@@ -960,6 +959,7 @@ void pmp_instance_destroy(pmp_instance *inst)
 {
     if (!inst)
         return;
+    DevicePool::FreeScope frees;
     inst->arena.release();
     host_words().give(inst->host_err);
     dfree(inst->h_masks);
@@ -1155,6 +1155,7 @@ struct pmp_hbp {
     int32_t h_cap = 0;
     ~pmp_hbp()
     {
+        DevicePool::FreeScope frees;
         dfree(rpi);
         dfree(re);
         dfree(rlen);
@@ -1175,6 +1176,7 @@ struct HbpScratch {
     HbpArgs h{};
     ~HbpScratch()
     {
+        DevicePool::FreeScope frees;
         dfree(h.key);
         dfree(h.slot_of);
         dfree(h.posinv);
@@ -1341,6 +1343,7 @@ pmp_status pmp_hbp_eval(pmp_hbp *hp, const uint64_t *masks, int32_t P, int64_t *
         return fail(PMP_EINVAL, "masks or fitness is NULL");
     pmp_instance *inst = hp->inst;
     hipStream_t s = (hipStream_t)stream;
+    const DevicePool::CallScope scope(s);
     const bool on_dev = flags & PMP_ON_DEVICE;
     const bool async = on_dev && (flags & PMP_ASYNC);
     const size_t W = inst->W;
@@ -1524,6 +1527,7 @@ pmp_status pmp_eval_population(pmp_instance *inst, const uint64_t *masks,
         return fail(PMP_EUNSUPPORTED, "the per-chromosome and per-client schemes take m <= %d",
                     PMP_MAX_FACILITIES);
     hipStream_t s = (hipStream_t)stream;
+    const DevicePool::CallScope scope(s);
     const bool on_dev = flags & PMP_ON_DEVICE;
     const bool async = on_dev && (flags & PMP_ASYNC);
     const size_t W = inst->W;
@@ -1695,6 +1699,7 @@ void pmp_ga_destroy(pmp_ga *ga)
 {
     if (!ga)
         return;
+    DevicePool::FreeScope frees;
     ga->arena.release();  // (clears its members: the frees below skip them)
     ga->parts.release();
     for (int k = 0; k < 2; ++k) {
@@ -2112,6 +2117,7 @@ pmp_status pmp_ga_step(pmp_ga *ga, int32_t generations, void *stream)
     if (generations == 0)
         return PMP_OK;
     hipStream_t s = (hipStream_t)stream;
+    const DevicePool::CallScope scope(s);
     if (!ga->persistent && ga->spec() && ga->ensure_spec() != hipSuccess)
         return fail(PMP_ENOMEM, "mutation-cycle buffers for P=%d, Y=%d", ga->prm.population,
                     ga->Y);
@@ -2722,6 +2728,7 @@ pmp_status pmp_features(pmp_instance *inst, const uint64_t *masks, int32_t P,
     if (inst->resolve_total() != hipSuccess)
         return fail(PMP_EDEVICE, "sum of d of the instance");
     hipStream_t s = (hipStream_t)stream;
+    const DevicePool::CallScope scope(s);
     const bool on_dev = flags & PMP_ON_DEVICE;
     const size_t W = inst->W, cells = (size_t)P * inst->m * kFeatures;
     const uint64_t *dm = masks;
@@ -2777,6 +2784,7 @@ void pmp_model_destroy(pmp_model *md)
 {
     if (!md)
         return;
+    DevicePool::FreeScope frees;
     dfree(md->d.master);
     dfree(md->d.m1);
     dfree(md->d.m2);
@@ -2859,6 +2867,7 @@ pmp_status model_stage(pmp_model *md, const float *x, const float *t, const floa
                        int32_t rows, bool on_dev, hipStream_t s, const float **dt,
                        const float **dw)
 {
+    const DevicePool::CallScope scope(s);
     if (md->cap < rows) {
         dfree(md->xf);
         dfree(md->xb);
@@ -3029,7 +3038,8 @@ pmp_status pmp_ga_set_model(pmp_ga *ga, pmp_model *model, const pmp_learn_params
         dalloc(&ga->rep_w, R) || dalloc(&ga->rep_jk, R * 2) || dalloc(&ga->rep_d, R * 2) ||
         dalloc(&ga->scores, P * C) || dalloc(&ga->cand, P * C * 2) ||
         dalloc(&ga->cbits, P * ga->inst->W) || dalloc(&ga->cpre, P * ga->inst->W) ||
-        hipMalloc(&ga->sums, P * kSlots * (2 * sizeof(uint32_t) + 3 * sizeof(uint64_t))) ||
+        DevicePool::get().alloc(&ga->sums,
+                                P * kSlots * (2 * sizeof(uint32_t) + 3 * sizeof(uint64_t))) ||
         dalloc(&ga->last_trained, 1)) {
         ga->free_learned();
         return fail(PMP_ENOMEM, "learned proposal buffers (%zu ring rows)", R);
