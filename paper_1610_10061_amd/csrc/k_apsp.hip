@@ -7,16 +7,22 @@
 // and min(d_ij, a + b) never exceeds d_ij <= INF: an update is one add and
 // one min.
 //
-// Per round kb (tile 64 x 64):
-//  - k_fw_panels: every workgroup first closes the diagonal tile (kb, kb)
-//    over its own 64 intermediate vertices (redundantly, in LDS), then one
-//    tile of row kb or of column kb through it; the workgroup of the
-//    diagonal itself stores it;
+// Per round kb (tile 64 x 64), two launches:
+//  - k_fw_panels: every tile of row kb and column kb times the closed diagonal
+//    tile G = (kb, kb): a row tile T becomes min over k of G[., k] + T[k, .],
+//    a column tile min over k of T[., k] + G[k, .] (G has a zero diagonal, so
+//    T itself is among the sums).  With G closed beforehand these are plain
+//    min-plus products, no chain of 64 dependent steps;
 //  - k_fw_rest: every other tile (i, j) takes min over k of
-//    D(i, kb)[., k] + D(kb, j)[k, .] - a min-plus product of the two panel
-//    tiles, staged in LDS, 4 x 4 elements per thread.
-#include <algorithm>
-
+//    D(i, kb)[., k] + D(kb, j)[k, .], and the workgroup of the next round's
+//    diagonal tile then closes it (the first round's is closed by k_fw_close).
+// When every panel workgroup closed the diagonal itself and relaxed its tile
+// step by step (128 barriers), a round's panels took 62 us whatever n; they
+// take 5 us now, k_fw_rest at n = 2000 23 us (20 before it also closed the
+// next diagonal, a chain of 16 barriers).  Whole calls, n = 900 / 2000 / 4096:
+// 1.27 / 2.76 / 7.8 -> 0.39 / 0.91 / 3.6 ms.  Bound: at n = 4096 the VALU (an
+// add and half a v_min3 per update: 19 of 26 T updates/s), at small n the
+// chain panels -> tile -> closing, about 25 us a round.
 #include "common.hpp"
 
 namespace pmp {
@@ -26,183 +32,181 @@ namespace {
 constexpr int kTile = 64;
 constexpr uint32_t kInf = 0x7FFFFFFFu;
 
-__device__ __forceinline__ uint32_t tile_at(const uint32_t *D, int ld, int ti, int tj, int r,
-                                            int c)
+constexpr int kLd = kTile + 4;  // padded LDS row: 16-byte aligned, columns spread over the banks
+
+__device__ __forceinline__ int64_t tile_row(int ld, int ti, int tj, int r)
 {
-    return D[(int64_t)(ti * kTile + r) * ld + tj * kTile + c];
+    return (int64_t)(ti * kTile + r) * ld + tj * kTile;
 }
 
-// A thread's 4 x 4 block of a 64 x 64 tile: rows 4 ty .. 4 ty + 3, columns
-// 4 tx .. 4 tx + 3 (ty = thread / 16, tx = thread % 16).
-struct Block {
-    uint32_t v[4][4];
-};
-
-__device__ __forceinline__ void load_block(Block &b, const uint32_t *D, int ld, int ti, int tj)
+// A 64 x 64 tile staged by 256 threads, as it is or transposed.
+__device__ __forceinline__ void stage_tile(uint32_t (&s)[kTile][kLd], const uint32_t *D, int ld,
+                                           int ti, int tj, bool transposed)
 {
-    const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
+    uint4 q[4];
+    const int r = (int)threadIdx.x >> 4, c = 4 * ((int)threadIdx.x & 15);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const uint4 q = *reinterpret_cast<const uint4 *>(
-            &D[(int64_t)(ti * kTile + 4 * ty + r) * ld + tj * kTile + 4 * tx]);
-        b.v[r][0] = q.x;
-        b.v[r][1] = q.y;
-        b.v[r][2] = q.z;
-        b.v[r][3] = q.w;
+    for (int k = 0; k < 4; ++k)
+        q[k] = *reinterpret_cast<const uint4 *>(D + tile_row(ld, ti, tj, r + 16 * k) + c);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int row = r + 16 * k;
+        if (transposed) {
+            s[c][row] = q[k].x;
+            s[c + 1][row] = q[k].y;
+            s[c + 2][row] = q[k].z;
+            s[c + 3][row] = q[k].w;
+        } else {
+            *reinterpret_cast<uint4 *>(&s[row][c]) = q[k];
+        }
     }
 }
 
-__device__ __forceinline__ void store_block(const Block &b, uint32_t *D, int ld, int ti, int tj)
+// Closes a tile over its own 64 vertices: wave v of 4 holds rows 16 v + r in
+// v[r], lane = column.  Four vertices at a time: their rows' owner closes the
+// four rows among themselves (register moves only), publishes them, and every
+// wave relaxes its rows through them: with the four rows closed, a row's new
+// values are the least of its old ones and of (its old entry at the vertex +
+// the vertex's row), so the four sums of a row do not wait for each other.
+// 16 barriers; 12 us against 29 us for 64 steps with a barrier each.
+__device__ __forceinline__ void close_tile(uint32_t (&v)[16], uint32_t (&pub)[2][4][kTile])
 {
-    const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    for (int owner = 0; owner < 4; ++owner) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-        *reinterpret_cast<uint4 *>(&D[(int64_t)(ti * kTile + 4 * ty + r) * ld + tj * kTile + 4 * tx]) =
-            make_uint4(b.v[r][0], b.v[r][1], b.v[r][2], b.v[r][3]);
-}
-
-// Row k and column k of a tile held in registers, published for step k:
-// the threads holding column k write it to col[k & 1], those holding row k
-// to row[k & 1].  Double buffering needs one barrier per step: a buffer is
-// rewritten two steps later, after every thread has passed the next barrier.
-struct Lines {
-    uint32_t row[2][kTile];
-    uint32_t col[2][kTile];
-};
-
-__device__ __forceinline__ void publish(const Block &b, Lines &L, int k, bool pub_row,
-                                        bool pub_col)
-{
-    const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
-    const int q = k & 3;  // selected, not indexed: a run-time index would spill the block
-    if (pub_col && tx == (k >> 2)) {
+        for (int g = 0; g < 4; ++g) {
+            const int k0 = 16 * owner + 4 * g;  // first of the four vertices
+            if (wave == owner) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-            L.col[k & 1][4 * ty + r] =
-                q == 0 ? b.v[r][0] : q == 1 ? b.v[r][1] : q == 2 ? b.v[r][2] : b.v[r][3];
-    }
-    if (pub_row && ty == (k >> 2)) {
+                for (int k = 0; k < 4; ++k)
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-            L.row[k & 1][4 * tx + c] =
-                q == 0 ? b.v[0][c] : q == 1 ? b.v[1][c] : q == 2 ? b.v[2][c] : b.v[3][c];
-    }
-}
-
-__device__ __forceinline__ void relax(Block &b, const uint32_t a[4], const uint32_t c[4])
-{
+                    for (int r = 0; r < 4; ++r)
+                        if (r != k)
+                            v[4 * g + r] =
+                                min(v[4 * g + r],
+                                    (uint32_t)__builtin_amdgcn_readlane((int)v[4 * g + r], k0 + k) +
+                                        v[4 * g + k]);
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+                for (int r = 0; r < 4; ++r)
+                    pub[g & 1][r][lane] = v[4 * g + r];
+            }
+            __syncthreads();
+            uint32_t row[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-            b.v[r][q] = min(b.v[r][q], a[r] + c[q]);
-}
-
-__device__ __forceinline__ void read4(const uint32_t *p, uint32_t out[4])
-{
-    const uint4 q = *reinterpret_cast<const uint4 *>(p);
-    out[0] = q.x;
-    out[1] = q.y;
-    out[2] = q.z;
-    out[3] = q.w;
-}
-
-// Close the diagonal tile over its own 64 vertices, in registers: step k
-// relaxes every entry through vertex k (row k and column k do not change
-// during step k, the diagonal entry being 0).
-__device__ __forceinline__ void close_diagonal(Block &g, Lines &L)
-{
-    const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
-    for (int k = 0; k < kTile; ++k) {
-        publish(g, L, k, true, true);
-        __syncthreads();
-        uint32_t a[4], c[4];
-        read4(&L.col[k & 1][4 * ty], a);
-        read4(&L.row[k & 1][4 * tx], c);
-        relax(g, a, c);
+            for (int k = 0; k < 4; ++k)
+                row[k] = pub[g & 1][k][lane];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                uint32_t x[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    x[k] = (uint32_t)__builtin_amdgcn_readlane((int)v[r], k0 + k) + row[k];
+                v[r] = min(min(min(min(v[r], x[0]), x[1]), x[2]), x[3]);  // two v_min3
+            }
+        }
     }
 }
 
-// Phases 1 and 2 of round kb.  Workgroup b < nb: row tile (kb, b);
-// nb <= b < 2 nb: column tile (b - nb, kb).  Every workgroup closes the
-// diagonal tile itself (no extra launch); the diagonal's own workgroups
-// (b = kb and b = nb + kb) stop there, and b = kb stores it.  A row tile
-// then relaxes through the closed diagonal's column k and its own row k, a
-// column tile through its own column k and the diagonal's row k.
+__global__ __launch_bounds__(256) void k_fw_close(uint32_t *D, int ld, int kb)
+{
+    __shared__ uint32_t pub[2][4][kTile];
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    uint32_t v[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+        v[r] = D[tile_row(ld, kb, kb, 16 * wave + r) + lane];
+    close_tile(v, pub);
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+        D[tile_row(ld, kb, kb, 16 * wave + r) + lane] = v[r];
+}
+
+// Phase 2 of round kb.  A workgroup takes a strip of 16 columns of a tile of
+// row kb, or of 16 rows of a tile of column kb (strips depend on themselves
+// and G only, so they are replaced in place): 8 (nb - 1) workgroups, four
+// sums per step and thread.
 __global__ __launch_bounds__(256) void k_fw_panels(uint32_t *D, int ld, int nb, int kb)
 {
-    __shared__ __attribute__((aligned(16))) Lines L;
-    // the closed diagonal: Gt[k][i] = G[i][k] (columns), G[k][j] (rows)
-    __shared__ __attribute__((aligned(16))) uint32_t Gt[kTile][kTile + 4];
-    __shared__ __attribute__((aligned(16))) uint32_t G[kTile][kTile + 4];
-    const int b = blockIdx.x;
-    const bool row = b < nb;
-    const int other = row ? b : b - nb;
-    const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
-    const bool diag = other == kb;
-    Block g, t;
-    load_block(g, D, ld, kb, kb);
-    if (!diag)
-        load_block(t, D, ld, row ? kb : other, row ? other : kb);
-    close_diagonal(g, L);
-    if (diag) {
-        if (row)
-            store_block(g, D, ld, kb, kb);
-        return;
+    __shared__ __attribute__((aligned(16))) uint32_t G[kTile][kLd];  // row strips: transposed
+    __shared__ __attribute__((aligned(16))) uint32_t T[kTile][20];   // T[k][strip position]
+    const int strips = 4 * (nb - 1);
+    const bool row = (int)blockIdx.x < strips;
+    const int x = row ? (int)blockIdx.x : (int)blockIdx.x - strips;
+    const int o = x >> 2, q = x & 3, other = o < kb ? o : o + 1;
+    const int t = (int)threadIdx.x;
+    if (row) {  // columns 16 q .. of tile (kb, other)
+        const int k = t >> 2, c = 4 * (t & 3);
+        const uint4 e = *reinterpret_cast<const uint4 *>(D + tile_row(ld, kb, other, k) + 16 * q + c);
+        *reinterpret_cast<uint4 *>(&T[k][c]) = e;
+    } else {  // rows 16 q .. of tile (other, kb)
+        const int r = t >> 4, k = 4 * (t & 15);
+        const uint4 e = *reinterpret_cast<const uint4 *>(D + tile_row(ld, other, kb, 16 * q + r) + k);
+        T[k][r] = e.x;
+        T[k + 1][r] = e.y;
+        T[k + 2][r] = e.z;
+        T[k + 3][r] = e.w;
     }
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            Gt[4 * tx + c][4 * ty + r] = g.v[r][c];
-            G[4 * ty + r][4 * tx + c] = g.v[r][c];
-        }
+    stage_tile(G, D, ld, kb, kb, row);
     __syncthreads();
+    // 16 strip positions x 64: this thread's strip position and four others
+    const int a = t >> 4, b = t & 15;
+    const int pos = row ? b : a, quad = 4 * (row ? a : b);
+    uint32_t acc[4] = {~0u, ~0u, ~0u, ~0u};
+#pragma unroll 16
     for (int k = 0; k < kTile; ++k) {
-        publish(t, L, k, row, !row);
-        __syncthreads();
-        uint32_t a[4], c[4];
-        if (row) {
-            read4(&Gt[k][4 * ty], a);
-            read4(&L.row[k & 1][4 * tx], c);
-        } else {
-            read4(&L.col[k & 1][4 * ty], a);
-            read4(&G[k][4 * tx], c);
-        }
-        relax(t, a, c);
+        const uint32_t s = T[k][pos];
+        const uint4 g = *reinterpret_cast<const uint4 *>(&G[k][quad]);
+        acc[0] = min(acc[0], g.x + s);
+        acc[1] = min(acc[1], g.y + s);
+        acc[2] = min(acc[2], g.z + s);
+        acc[3] = min(acc[3], g.w + s);
     }
-    store_block(t, D, ld, row ? kb : other, row ? other : kb);
+    if (row) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            D[tile_row(ld, kb, other, quad + r) + 16 * q + pos] = acc[r];
+    } else {
+        *reinterpret_cast<uint4 *>(D + tile_row(ld, other, kb, 16 * q + pos) + quad) =
+            make_uint4(acc[0], acc[1], acc[2], acc[3]);
+    }
 }
 
 // Phase 3 of round kb: tile (i, j) off row and column kb.  The column-panel
 // tile is staged transposed so each thread reads its 4 rows' entries of
 // column k with one 16-byte LDS read, and the row-panel tile's 4 columns of
-// row k likewise.
+// row k likewise (4 x 4 sums per thread and step).  The workgroup of tile
+// (kb + 1, kb + 1), the first dispatched, closes it afterwards: its waves run
+// at a higher priority than the ones they share a CU with, so that its chain
+// ends with the launch's other work and not after it.
 __global__ __launch_bounds__(256) void k_fw_rest(uint32_t *D, int ld, int nb, int kb)
 {
-    // rows padded by 4 words: the transposing stores spread over the banks,
-    // and rows stay 16-byte aligned
-    __shared__ __attribute__((aligned(16))) uint32_t At[kTile][kTile + 4];  // At[k][i] = D(i, kb)[i][k]
-    __shared__ __attribute__((aligned(16))) uint32_t B[kTile][kTile + 4];   // B[k][j] = D(kb, j)[k][j]
+    __shared__ __attribute__((aligned(16))) uint32_t At[kTile][kLd];  // At[k][i] = D(i, kb)[i][k]
+    __shared__ __attribute__((aligned(16))) uint32_t B[kTile][kLd];   // B[k][j] = D(kb, j)[k][j]
+    __shared__ uint32_t pub[2][4][kTile];
     const int nrest = nb - 1;
-    const int ii = blockIdx.x / nrest, jj = blockIdx.x - ii * nrest;
+    // tiles in order from (kb, kb) of the numbering that leaves out row and
+    // column kb: that is tile (kb + 1, kb + 1) while there is one
+    int x = (int)blockIdx.x + (kb < nrest ? kb * nrest + kb : 0);
+    if (x >= nrest * nrest)
+        x -= nrest * nrest;
+    const int ii = x / nrest, jj = x - ii * nrest;
     const int ti = ii < kb ? ii : ii + 1, tj = jj < kb ? jj : jj + 1;
-    for (int e = threadIdx.x; e < kTile * kTile; e += 256) {
-        const int r = e >> 6, c = e & 63;
-        At[c][r] = tile_at(D, ld, ti, kb, r, c);
-        B[r][c] = tile_at(D, ld, kb, tj, r, c);
-    }
+    const bool next_diag = ti == kb + 1 && tj == kb + 1;
+    if (next_diag)
+        __builtin_amdgcn_s_setprio(3);
     const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
     uint32_t acc[4][4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const uint4 v = *reinterpret_cast<const uint4 *>(
-            &D[(int64_t)(ti * kTile + 4 * ty + r) * ld + tj * kTile + 4 * tx]);
+        const uint4 v =
+            *reinterpret_cast<const uint4 *>(D + tile_row(ld, ti, tj, 4 * ty + r) + 4 * tx);
         acc[r][0] = v.x;
         acc[r][1] = v.y;
         acc[r][2] = v.z;
         acc[r][3] = v.w;
     }
+    stage_tile(At, D, ld, ti, kb, true);
+    stage_tile(B, D, ld, kb, tj, false);
     __syncthreads();
 #pragma unroll 8
     for (int k = 0; k < kTile; ++k) {
@@ -216,53 +220,96 @@ __global__ __launch_bounds__(256) void k_fw_rest(uint32_t *D, int ld, int nb, in
             for (int c = 0; c < 4; ++c)
                 acc[r][c] = min(acc[r][c], av[r] + bv[c]);
     }
+    if (next_diag) {
+        __syncthreads();  // (At is read no more)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            *reinterpret_cast<uint4 *>(&At[4 * ty + r][4 * tx]) =
+                make_uint4(acc[r][0], acc[r][1], acc[r][2], acc[r][3]);
+        __syncthreads();
+        const int lane = threadIdx.x & 63, wave = wave_id();
+        uint32_t v[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            v[r] = At[16 * wave + r][lane];
+        close_tile(v, pub);
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            D[tile_row(ld, ti, tj, 16 * wave + r) + lane] = v[r];
+        return;
+    }
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-        *reinterpret_cast<uint4 *>(&D[(int64_t)(ti * kTile + 4 * ty + r) * ld + tj * kTile + 4 * tx]) =
+        *reinterpret_cast<uint4 *>(D + tile_row(ld, ti, tj, 4 * ty + r) + 4 * tx) =
             make_uint4(acc[r][0], acc[r][1], acc[r][2], acc[r][3]);
 }
 
+// Rows that a workgroup of k_fw_in and k_fw_out takes (256 columns each).
+constexpr int kInRows = 16;
+
 // Work matrix from the weights: INF where there is no edge (w < 0) and in the
-// padding, 0 on the diagonal, and the largest weight into *wmax (a grid-stride
-// loop, so that only a few thousand waves meet at the one atomic).
+// padding, 0 on the diagonal, and the largest weight into *wmax (one atomic
+// per workgroup at most: one per wave kept 8192 of them on one address for
+// 80 us at n = 2000).
 __global__ __launch_bounds__(256) void k_fw_in(const int32_t *w, int64_t ldw, int n, uint32_t *D,
                                                int ld, uint32_t *wmax)
 {
-    const int64_t cells = (int64_t)ld * ld;
+    __shared__ uint32_t part[4];
+    const int j = (int)blockIdx.x * 256 + (int)threadIdx.x, i0 = (int)blockIdx.y * kInRows;
     uint32_t mx = 0;
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < cells;
-         e += (int64_t)gridDim.x * 256) {
-        const int i = (int)(e / ld), j = (int)(e - (int64_t)i * ld);
+    int32_t x[kInRows];
+#pragma unroll
+    for (int r = 0; r < kInRows; ++r)
+        x[r] = w[(int64_t)min(i0 + r, n - 1) * ldw + min(j, n - 1)];
+#pragma unroll
+    for (int r = 0; r < kInRows; ++r) {
+        const int i = i0 + r;
         uint32_t v = kInf;
-        if (i < n && j < n) {
-            const int32_t x = w[(int64_t)i * ldw + j];
-            if (x >= 0) {
-                v = (uint32_t)x;
-                mx = max(mx, v);
-            }
+        if (i < n && j < n && x[r] >= 0) {
+            v = (uint32_t)x[r];
+            mx = max(mx, v);
         }
         if (i == j)
             v = 0;
-        D[e] = v;
+        if (i < ld && j < ld)
+            D[(int64_t)i * ld + j] = v;
     }
-    // one atomic per wave (every lane takes part in the shuffles)
 #pragma unroll
     for (int dd = 32; dd > 0; dd >>= 1)
         mx = max(mx, (uint32_t)__shfl_xor((int)mx, dd));
-    if ((threadIdx.x & 63) == 0 && mx > 0)
-        atomicMax(wmax, mx);
+    if ((threadIdx.x & 63) == 0)
+        part[threadIdx.x >> 6] = mx;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        mx = max(max(part[0], part[1]), max(part[2], part[3]));
+        if (mx > __hip_atomic_load(wmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicMax(wmax, mx);
+    }
 }
 
-// Distances out: -1 for INF (no path).
+// Distances out: -1 for INF (no path).  Nothing is written when a path length
+// might not fit ((n - 1) * largest weight >= INF); the largest weight goes to
+// the host word for the caller's check.
 __global__ __launch_bounds__(256) void k_fw_out(const uint32_t *D, int ld, int n, int32_t *d,
-                                                int64_t ldd)
+                                                int64_t ldd, const uint32_t *wmax,
+                                                uint32_t *host_wmax)
 {
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e >= (int64_t)n * n)
+    const uint32_t mx = *wmax;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
+        __hip_atomic_store(host_wmax, mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if ((uint64_t)(n - 1) * mx >= kInf)
         return;
-    const int i = (int)(e / n), j = (int)(e - (int64_t)i * n);
-    const uint32_t v = D[(int64_t)i * ld + j];
-    d[(int64_t)i * ldd + j] = v >= kInf ? -1 : (int32_t)v;
+    const int j = (int)blockIdx.x * 256 + (int)threadIdx.x, i0 = (int)blockIdx.y * kInRows;
+    if (j >= n)
+        return;
+#pragma unroll
+    for (int r = 0; r < kInRows; ++r) {
+        const int i = i0 + r;
+        if (i < n) {
+            const uint32_t v = D[(int64_t)i * ld + j];
+            d[(int64_t)i * ldd + j] = v >= kInf ? -1 : (int32_t)v;
+        }
+    }
 }
 
 }  // namespace
@@ -276,30 +323,28 @@ hipError_t launch_apsp_in(const int32_t *w, int64_t ldw, int n, uint32_t *D, uin
                           hipStream_t s)
 {
     const int ld = apsp_padded(n);
-    const int64_t cells = (int64_t)ld * ld;
-    const int64_t blocks = std::min<int64_t>((cells + 255) / 256, 2048);
-    hipLaunchKernelGGL(k_fw_in, dim3((unsigned)blocks), dim3(256), 0, s, w, ldw, n, D, ld, wmax);
+    hipLaunchKernelGGL(k_fw_in, dim3((ld + 255) / 256, (ld + kInRows - 1) / kInRows), dim3(256), 0,
+                       s, w, ldw, n, D, ld, wmax);
     return hipGetLastError();
 }
 
 hipError_t launch_apsp_rounds(uint32_t *D, int n, hipStream_t s)
 {
     const int ld = apsp_padded(n), nb = ld / kTile;
-    for (int kb = 0; kb < nb; ++kb) {
-        hipLaunchKernelGGL(k_fw_panels, dim3(2 * nb), dim3(256), 0, s, D, ld, nb, kb);
-        if (nb > 1)
-            hipLaunchKernelGGL(k_fw_rest, dim3((nb - 1) * (nb - 1)), dim3(256), 0, s, D, ld, nb,
-                               kb);
+    hipLaunchKernelGGL(k_fw_close, dim3(1), dim3(256), 0, s, D, ld, 0);
+    for (int kb = 0; kb < nb && nb > 1; ++kb) {
+        hipLaunchKernelGGL(k_fw_panels, dim3(8 * (nb - 1)), dim3(256), 0, s, D, ld, nb, kb);
+        hipLaunchKernelGGL(k_fw_rest, dim3((nb - 1) * (nb - 1)), dim3(256), 0, s, D, ld, nb, kb);
     }
     return hipGetLastError();
 }
 
-hipError_t launch_apsp_out(const uint32_t *D, int n, int32_t *d, int64_t ldd, hipStream_t s)
+hipError_t launch_apsp_out(const uint32_t *D, int n, int32_t *d, int64_t ldd,
+                           const uint32_t *wmax, uint32_t *host_wmax, hipStream_t s)
 {
     const int ld = apsp_padded(n);
-    const int64_t cells = (int64_t)n * n;
-    hipLaunchKernelGGL(k_fw_out, dim3((unsigned)((cells + 255) / 256)), dim3(256), 0, s, D, ld, n,
-                       d, ldd);
+    hipLaunchKernelGGL(k_fw_out, dim3((n + 255) / 256, (n + kInRows - 1) / kInRows), dim3(256), 0,
+                       s, D, ld, n, d, ldd, wmax, host_wmax);
     return hipGetLastError();
 }
 

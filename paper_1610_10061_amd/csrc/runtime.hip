@@ -1419,7 +1419,7 @@ void pmp_hbp_destroy(pmp_hbp *hp)
 struct ApspCache {
     std::mutex mu;
     struct Dev {
-        uint32_t *work = nullptr, *wmax = nullptr;
+        uint32_t *work = nullptr, *wmax = nullptr, *host_wmax = nullptr;
         int32_t *w = nullptr, *d = nullptr;  // staging for host arguments
         size_t work_cap = 0, stage_cap = 0;
     };
@@ -1458,6 +1458,8 @@ pmp_status pmp_apsp(const int32_t *w, int64_t ldw, int32_t n, int32_t *d, int64_
     }
     if (!b.wmax && dalloc(&b.wmax, 1) != hipSuccess)
         return fail(PMP_ENOMEM, "APSP word");
+    if (!b.host_wmax && !(b.host_wmax = host_words().take()))
+        return fail(PMP_ENOMEM, "pinned host memory");
     const int32_t *dw = w;
     int32_t *dd = d;
     int64_t ldw_dev = ldw, ldd_dev = ldd;
@@ -1479,17 +1481,19 @@ pmp_status pmp_apsp(const int32_t *w, int64_t ldw, int32_t n, int32_t *d, int64_
     }
     HIP_TRY(launch_zero(b.wmax, sizeof(uint32_t), s));
     HIP_TRY(launch_apsp_in(dw, ldw_dev, n, b.work, b.wmax, s));
-    uint32_t wmax = 0;
-    HIP_TRY(hipMemcpyAsync(&wmax, b.wmax, sizeof wmax, hipMemcpyDeviceToHost, s));
+    HIP_TRY(launch_apsp_rounds(b.work, n, s));
+    HIP_TRY(launch_apsp_out(b.work, n, dd, ldd_dev, b.wmax, b.host_wmax, s));
     HIP_TRY(hipStreamSynchronize(s));
+    // (an update never exceeds INF, so with weights too large for int32 paths
+    // the rounds have only been of no use)
+    const uint32_t wmax = *b.host_wmax;
     if ((int64_t)(n - 1) * (int64_t)wmax >= 0x7FFFFFFFll)
         return fail(PMP_EUNSUPPORTED, "path lengths may exceed int32: (n-1) * max weight = %lld",
                     (long long)(n - 1) * (long long)wmax);
-    HIP_TRY(launch_apsp_rounds(b.work, n, s));
-    HIP_TRY(launch_apsp_out(b.work, n, dd, ldd_dev, s));
-    if (!on_dev)
-        HIP_TRY(hipMemcpy2DAsync(d, (size_t)ldd * 4, b.d, (size_t)n * 4, (size_t)n * 4, n,
-                                 hipMemcpyDeviceToHost, s));
+    if (on_dev)
+        return PMP_OK;
+    HIP_TRY(hipMemcpy2DAsync(d, (size_t)ldd * 4, b.d, (size_t)n * 4, (size_t)n * 4, n,
+                             hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     return PMP_OK;
 }
