@@ -248,16 +248,42 @@ int eval_waves(int n, int P, int m, int p, int W)
     return 16;
 }
 
+// Compute units of the current device (queried once per device).
+int device_cus()
+{
+    static std::atomic<int> cus_of[64];
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64) {
+        cus = cus_of[dev].load(std::memory_order_relaxed);
+        if (cus == 0 &&
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess)
+            cus_of[dev].store(cus, std::memory_order_relaxed);
+    }
+    return cus < 1 ? 256 : cus;
+}
+
 // Clients per workgroup of the fused stage-and-evaluation launches.  Each
-// client tile's workgroup repeats the stage step of its 64 chromosomes, so
-// these tiles are larger than the plain evaluation's: about 512 workgroups,
-// 64 clients at least.  PMP_FUSED_CLIENTS forces it.
+// client tile's workgroup repeats the stage step of its 64 chromosomes, and a
+// CU holds one such workgroup, so the launch lasts a stage step and the walk
+// of one workgroup's clients as long as every workgroup has a CU: the fewest
+// clients (a multiple of the 16 waves) for which they do, but at most 32 client
+// tiles, whose partial sums the next stage loads in one round.  A generation
+// at n = 100, P = 64: 65.6 us with 64 clients, 58.1 with 16; n = 600, P = 512:
+// 120 with 64, 107 with 32, 148 with 16 (304 workgroups); n = 900, P = 64: 71.4
+// with 64, 69.4 with 32, 71.6 with 16 (57 tiles).  When 64 clients leave more
+// workgroups than CUs, about 512 workgroups.  PMP_FUSED_CLIENTS forces it.
 int fused_clients_per_block(int n, int P)
 {
     const int forced = env_int("PMP_FUSED_CLIENTS", 0);
     if (forced > 0)
         return forced;
     const long tiles_c = (P + kEvalTile - 1) / kEvalTile;
+    const long fit = device_cus() / tiles_c;  // client tiles that leave a CU each
+    for (long f = 16; f < 64 && f < n; f += 16) {
+        const long ti = ((long)n + f - 1) / f;
+        if (ti <= 32 && ti <= fit)
+            return (int)f;
+    }
     const long ti = std::max(1L, 512 / std::max(1L, tiles_c));
     long f = ((long)n + ti - 1) / ti;
     f = std::max(f, 64L);
@@ -278,16 +304,7 @@ int clients_per_block(int n, int P, int m, int p, int W, bool reduced = false,
         return (int)(((cpb + waves - 1) / waves) * waves);
     }
     const bool paired = paired_scans(m, p) != 0;
-    static std::atomic<int> cus_of[64];  // per device, queried once
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64) {
-        cus = cus_of[dev].load(std::memory_order_relaxed);
-        if (cus == 0 &&
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess)
-            cus_of[dev].store(cus, std::memory_order_relaxed);
-    }
-    if (cus < 1)
-        cus = 256;
+    const int cus = device_cus();
     const long slots = (long)cus * eval_workgroups_per_cu(W, reduced, paired, waves);
     // When the CUs hold fewer than 3.5 workgroups each, fill the slots once;
     // else aim at about 2.75 per CU (G900: 20 clients per workgroup measured
@@ -305,6 +322,22 @@ int clients_per_block(int n, int P, int m, int p, int W, bool reduced = false,
     if (cpb < 64 && want < slots && cpb >= unit)
         cpb -= cpb % unit;
     return (int)cpb;
+}
+
+// Clients per workgroup of a GA run's population evaluation: the rule above,
+// but no more client tiles than the stage that adds up their partial sums
+// loads in one round, 16 (a row of 16 lanes per chromosome) when the crossover
+// stages are fused with their evaluations, else 64.  A generation at n = 900,
+// P = 64: 114 us with the rule's 4 clients, 71 with 64; n = 400, P = 256: 99
+// and 86 (with 32); n = 1500, P = 256 (not fused): 123 and 112 (with 32).
+int ga_clients_per_block(int n, int P, int m, int p, int W, int waves, bool fused)
+{
+    const int cpb = clients_per_block(n, P, m, p, W, false, waves);
+    if (env_int("PMP_CLIENTS_PER_BLOCK", 0) > 0)
+        return cpb;
+    const int most = fused ? 16 : 64;
+    const int least = (n + most - 1) / most;
+    return std::max(cpb, (least + waves - 1) / waves * waves);
 }
 
 // binom[a (p + 1) + b] = C(a, b) for a < m, b <= p, by Pascal's rule,
@@ -1779,7 +1812,7 @@ pmp_status pmp_ga_create(pmp_instance *inst, const pmp_ga_params *prm,
     ga->waves = eval_waves(inst->n, P, inst->m, inst->p, inst->W);
     ga->spec_waves = ga->waves;
     ga->fused = env_int("PMP_GA_FUSED", 1) != 0 && ga_stage_eval_fits(inst->W);
-    ga->cpb = clients_per_block(inst->n, P, inst->m, inst->p, inst->W, false, ga->waves);
+    ga->cpb = ga_clients_per_block(inst->n, P, inst->m, inst->p, inst->W, ga->waves, ga->fused);
     ga->TI = (inst->n + ga->cpb - 1) / ga->cpb;
     ga->fcpb = fused_clients_per_block(inst->n, P);
     ga->fTI = (inst->n + ga->fcpb - 1) / ga->fcpb;
