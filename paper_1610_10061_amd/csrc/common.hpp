@@ -149,10 +149,12 @@ constexpr int kEvalWaves = 4;     // waves per block
 constexpr int kMaxLdsRow = 23552;
 
 // Launchers (each lives with its kernels).
+// (m <= kMaxLdsRow; row_err[i] = 1 for a row with a negative distance, else 0;
+// colsum and nearc, m each, are zeroed)
 hipError_t launch_sort_rows(const int32_t *d, int64_t ld, int32_t n, int32_t m,
                             int32_t K, int32_t pitch, uint16_t *pi,
-                            int32_t *delta, int32_t *ds, uint32_t *err,
-                            hipStream_t s);
+                            int32_t *delta, int32_t *ds, uint32_t *row_err,
+                            unsigned long long *colsum, uint32_t *nearc, hipStream_t s);
 // e0/e1 (optional) are recorded at the kernel's start and end.
 // Workgroups of the evaluation kernel for W words per chromosome (reduced
 // or paired walk) that one CU holds at once.

@@ -229,7 +229,9 @@ __global__ __launch_bounds__(64 * NW, radix_waves_per_simd(NW, I)) void k_radix_
                                                         uint16_t *__restrict__ pi,
                                                         int32_t *__restrict__ delta,
                                                         int32_t *__restrict__ ds,
-                                                        uint32_t *__restrict__ err)
+                                                        uint32_t *__restrict__ row_err,
+                                                        unsigned long long *__restrict__ colsum,
+                                                        uint32_t *__restrict__ nearc)
 {
     extern __shared__ __align__(16) uint32_t lds_words[];
     __shared__ uint32_t wave_word[NW];
@@ -262,8 +264,14 @@ __global__ __launch_bounds__(64 * NW, radix_waves_per_simd(NW, I)) void k_radix_
     any = __builtin_amdgcn_readfirstlane(any);
     __syncthreads();  // (wave_word is used again)
     const int bits = any ? 32 - __builtin_clz(any) : 0;
-    if ((int32_t)any < 0 && threadIdx.x == 0)
-        atomicOr(err, ERR_NEGATIVE_DISTANCE);
+    if (threadIdx.x == 0)
+        row_err[i] = any >> 31;  // a negative distance
+    // this row's share of the sums that the next launch adds to
+    for (int64_t j = i + (int64_t)gridDim.x * threadIdx.x; j < m;
+         j += (int64_t)gridDim.x * 64 * NW) {
+        colsum[j] = 0ull;
+        nearc[j] = 0u;
+    }
     // padding past m: the last keys of every pass's last digit
     if (bits <= 16) {
 #pragma unroll
@@ -479,7 +487,8 @@ namespace {
 
 template <int NW, int I>
 hipError_t launch_radix(const int32_t *d, int64_t ld, int32_t n, int32_t m, int32_t K,
-                        int32_t pitch, uint16_t *pi, int32_t *delta, int32_t *ds, uint32_t *err,
+                        int32_t pitch, uint16_t *pi, int32_t *delta, int32_t *ds,
+                        uint32_t *row_err, unsigned long long *colsum, uint32_t *nearc,
                         hipStream_t s)
 {
     static_assert(NW * I * 64 <= 65535, "places are counted in 16 bits");
@@ -494,7 +503,7 @@ hipError_t launch_radix(const int32_t *d, int64_t ld, int32_t n, int32_t m, int3
             return e;
     }
     hipLaunchKernelGGL((k_radix_rows<NW, I>), dim3(n), dim3(64 * NW), lds, s, d, ld, m, K, pitch,
-                       pi, delta, ds, err);
+                       pi, delta, ds, row_err, colsum, nearc);
     return hipGetLastError();
 }
 
@@ -503,12 +512,13 @@ hipError_t launch_radix(const int32_t *d, int64_t ld, int32_t n, int32_t m, int3
 // m <= kMaxLdsRow.
 hipError_t launch_sort_rows(const int32_t *d, int64_t ld, int32_t n, int32_t m,
                             int32_t K, int32_t pitch, uint16_t *pi,
-                            int32_t *delta, int32_t *ds, uint32_t *err,
-                            hipStream_t s)
+                            int32_t *delta, int32_t *ds, uint32_t *row_err,
+                            unsigned long long *colsum, uint32_t *nearc, hipStream_t s)
 {
 #define PMP_RADIX(NW, I)                                                                \
     if (m <= NW * I * 64)                                                               \
-        return launch_radix<NW, I>(d, ld, n, m, K, pitch, pi, delta, ds, err, s);
+        return launch_radix<NW, I>(d, ld, n, m, K, pitch, pi, delta, ds, row_err, colsum,       \
+                                   nearc, s);
     PMP_RADIX(2, 1)
     PMP_RADIX(2, 2)
     PMP_RADIX(4, 2)

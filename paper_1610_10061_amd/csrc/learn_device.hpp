@@ -289,11 +289,14 @@ hipError_t launch_features(const Tables &t, const uint64_t *masks, int P, const 
 // The proposal of one generation (candidates, walk, scoring and picks);
 // `in` is the buffer the finished crossover stages read.
 hipError_t launch_propose(const LearnArgs &a, int in, hipStream_t s);
-// Column sums of d and near counts (first L entries of the Pi' rows); then
-// report[0] = the sum of d, report[1] = the error word err (one read-back).
+// Column sums of d and near counts (first L entries of the Pi' rows) added to
+// colsum and nearc (zeroed before); then the sum of d into *total and the
+// error word, from the rows' flags if there are any, into *err, and both into
+// host[2..3] and host[0] when host is given.
 hipError_t launch_static_sums(const int32_t *d, int64_t ld, int n, int m, const uint16_t *pi,
                               int pitch, int L, unsigned long long *colsum, uint32_t *nearc,
-                              const uint32_t *err, unsigned long long *report, hipStream_t s);
+                              const uint32_t *row_err, uint32_t *err, uint32_t *err_now,
+                              unsigned long long *total, uint32_t *host, hipStream_t s);
 
 // Load a chromosome into LDS (as 32-bit words) and check it: exactly p
 // open facilities, no bits at positions >= m.  Block-wide; returns the

@@ -56,6 +56,18 @@ hipError_t dalloc(T **p, size_t count)
     return DevicePool::get().alloc((void **)p, sizeof(T) * count);
 }
 
+// `rows` rows of `words` 32-bit words between arrays of row strides ldd and
+// lds, as one block when neither has gaps (a strided copy from pageable
+// memory goes row by row: 900 rows of 900 took 8.5 ms, the block 0.4).
+hipError_t copy_rows(int32_t *dst, int64_t ldd, const int32_t *src, int64_t lds, int64_t words,
+                     int64_t rows, hipMemcpyKind kind, hipStream_t s)
+{
+    if (ldd == words && lds == words)
+        return hipMemcpyAsync(dst, src, sizeof(int32_t) * (size_t)(words * rows), kind, s);
+    return hipMemcpy2DAsync(dst, sizeof(int32_t) * (size_t)ldd, src, sizeof(int32_t) * (size_t)lds,
+                            sizeof(int32_t) * (size_t)words, (size_t)rows, kind, s);
+}
+
 template <class T>
 void dfree(T *&p)
 {
@@ -109,10 +121,11 @@ Staging &staging()
     return st;
 }
 
-// Pinned host words, one per live instance, that a waiting evaluation's
-// error bits are stored to by its last kernel (an instance takes its word
-// when it is made, so that evaluations allocate nothing).  Pages of words
-// are kept until the process ends; words are handed out again.
+// Pinned host memory, four 32-bit words per live instance, that kernels store
+// what a waiting call reads back to: error bits (word 0) and the sum of d
+// (words 2 and 3).  An instance takes its words when it is made, so that
+// evaluations allocate nothing.  Pages are kept until the process ends; words
+// are handed out again.
 struct HostWords {
     std::mutex mu;
     std::vector<uint32_t *> spare;
@@ -126,7 +139,7 @@ struct HostWords {
             if (hipHostMalloc((void **)&page, sizeof(uint32_t) * kPage, hipHostMallocPortable) !=
                 hipSuccess)
                 return nullptr;
-            for (size_t k = 0; k < kPage; ++k)
+            for (size_t k = 0; k < kPage; k += 4)
                 spare.push_back(page + k);
         }
         uint32_t *w = spare.back();
@@ -405,8 +418,9 @@ struct pmp_instance {
     mutable int64_t total = 0;             // sum of d
     mutable bool total_pending = false;    // not read back yet (asynchronous preprocessing)
     int32_t near_len = 1;                  // ceil(m / p)
-    unsigned long long *dtotal = nullptr;  // the sum and the error word, read back together
-    Arena arena;                           // pi, ds, delta, err, colsum, nearc, dtotal
+    unsigned long long *dtotal = nullptr;  // the sum on the device
+    uint32_t *row_err = nullptr;           // n flags of the sort: negative distances
+    Arena arena;                           // pi, ds, delta, err, colsum, nearc, dtotal, row_err
 
     // the sum of d, read back on its first use after an asynchronous
     // preprocessing (which may still be running on its stream)
@@ -1048,7 +1062,8 @@ pmp_status pmp_preprocess(const int32_t *d, int64_t ld, int32_t n, int32_t m,
     inst->arena.add(&inst->err, 64);
     inst->arena.add(&inst->colsum, (size_t)m);
     inst->arena.add(&inst->nearc, (size_t)m);
-    inst->arena.add(&inst->dtotal, 2);
+    inst->arena.add(&inst->dtotal, 1);
+    inst->arena.add(&inst->row_err, (size_t)n);
     if (inst->arena.carve() != hipSuccess) {
         pmp_instance_destroy(inst);
         return fail(PMP_ENOMEM, "device allocation of tables (%zu cells)", cells);
@@ -1065,18 +1080,13 @@ pmp_status pmp_preprocess(const int32_t *d, int64_t ld, int32_t n, int32_t m,
     int64_t src_ld = ld;
     pmp_status st = PMP_OK;
     do {
-        hipError_t e = hipMemsetAsync(inst->err, 0, 64 * sizeof(uint32_t), s);
-        if (e != hipSuccess) {
-            st = fail(PMP_EDEVICE, "hipMemsetAsync: %s", hipGetErrorString(e));
-            break;
-        }
+        hipError_t e = hipSuccess;
         if (!on_dev) {
             if (dalloc(&dd, (size_t)n * m) != hipSuccess) {
                 st = fail(PMP_ENOMEM, "device copy of d");
                 break;
             }
-            e = hipMemcpy2DAsync(dd, sizeof(int32_t) * m, d, sizeof(int32_t) * ld,
-                                 sizeof(int32_t) * m, n, hipMemcpyHostToDevice, s);
+            e = copy_rows(dd, m, d, ld, m, n, hipMemcpyHostToDevice, s);
             if (e != hipSuccess) {
                 st = fail(PMP_EDEVICE, "copy of d: %s", hipGetErrorString(e));
                 break;
@@ -1084,9 +1094,10 @@ pmp_status pmp_preprocess(const int32_t *d, int64_t ld, int32_t n, int32_t m,
             src = dd;
             src_ld = m;
         }
-        if (m <= kMaxLdsRow) {
-            e = launch_sort_rows(src, src_ld, n, m, inst->K, inst->pitch, inst->pi,
-                                 inst->delta, inst->ds, inst->err, s);
+        const bool in_lds = m <= kMaxLdsRow;
+        if (in_lds) {
+            e = launch_sort_rows(src, src_ld, n, m, inst->K, inst->pitch, inst->pi, inst->delta,
+                                 inst->ds, inst->row_err, inst->colsum, inst->nearc, s);
         } else {  // rows wider than one workgroup's LDS: the sort in device memory
             int32_t m2 = 2;
             while (m2 < m)
@@ -1096,34 +1107,38 @@ pmp_status pmp_preprocess(const int32_t *d, int64_t ld, int32_t n, int32_t m,
                 st = fail(PMP_ENOMEM, "sort scratch (%d rows x %d keys)", batch, m2);
                 break;
             }
-            e = launch_sort_rows_wide(src, src_ld, n, m, inst->K, inst->pitch, inst->pi,
-                                      inst->delta, inst->ds, inst->err, wide, batch, s);
+            e = launch_zero(inst->err, sizeof(uint32_t), s);
+            if (e == hipSuccess)
+                e = launch_zero(inst->colsum, sizeof(unsigned long long) * m, s);
+            if (e == hipSuccess)
+                e = launch_zero(inst->nearc, sizeof(uint32_t) * m, s);
+            if (e == hipSuccess)
+                e = launch_sort_rows_wide(src, src_ld, n, m, inst->K, inst->pitch, inst->pi,
+                                          inst->delta, inst->ds, inst->err, wide, batch, s);
         }
         if (e != hipSuccess) {
             st = fail(PMP_EDEVICE, "sort kernel launch: %s", hipGetErrorString(e));
             break;
         }
-        // static sums of the learned proposal's features; the sum of d and
-        // the error word come back in one copy
-        e = hipMemsetAsync(inst->colsum, 0, sizeof(unsigned long long) * m, s);
-        if (e == hipSuccess)
-            e = hipMemsetAsync(inst->nearc, 0, sizeof(uint32_t) * m, s);
-        if (e == hipSuccess)
-            e = launch_static_sums(src, src_ld, n, m, inst->pi, inst->pitch, inst->near_len,
-                                   inst->colsum, inst->nearc, inst->err, inst->dtotal, s);
+        // static sums of the learned proposal's features, and the error word
+        e = launch_static_sums(src, src_ld, n, m, inst->pi, inst->pitch, inst->near_len,
+                               inst->colsum, inst->nearc, in_lds ? inst->row_err : nullptr,
+                               inst->err, inst->err_now, inst->dtotal,
+                               async ? nullptr : inst->host_err, s);
         if (e == hipSuccess && async) {  // the error word stays for pmp_instance_check
             inst->total_pending = true;
             break;
         }
-        std::vector<unsigned long long> rb;
         if (e == hipSuccess)
-            e = staging().read(inst->dtotal, 2, s, rb);
+            e = hipStreamSynchronize(s);
         if (e != hipSuccess) {
             st = fail(PMP_EDEVICE, "preprocess: %s", hipGetErrorString(e));
             break;
         }
-        inst->total = (int64_t)rb[0];
-        st = status_from_err((uint32_t)rb[1]);
+        unsigned long long total = 0;
+        memcpy(&total, inst->host_err + 2, sizeof total);
+        inst->total = (int64_t)total;
+        st = status_from_err(*inst->host_err);
     } while (0);
     dfree(dd);
     dfree(wide);
@@ -1506,8 +1521,7 @@ pmp_status pmp_apsp(const int32_t *w, int64_t ldw, int32_t n, int32_t *d, int64_
                 return fail(PMP_ENOMEM, "APSP staging (n=%d)", n);
             b.stage_cap = nn;
         }
-        HIP_TRY(hipMemcpy2DAsync(b.w, (size_t)n * 4, w, (size_t)ldw * 4, (size_t)n * 4, n,
-                                 hipMemcpyHostToDevice, s));
+        HIP_TRY(copy_rows(b.w, n, w, ldw, n, n, hipMemcpyHostToDevice, s));
         dw = b.w;
         dd = b.d;
         ldw_dev = ldd_dev = n;
@@ -1525,8 +1539,7 @@ pmp_status pmp_apsp(const int32_t *w, int64_t ldw, int32_t n, int32_t *d, int64_
                     (long long)(n - 1) * (long long)wmax);
     if (on_dev)
         return PMP_OK;
-    HIP_TRY(hipMemcpy2DAsync(d, (size_t)ldd * 4, b.d, (size_t)n * 4, (size_t)n * 4, n,
-                             hipMemcpyDeviceToHost, s));
+    HIP_TRY(copy_rows(d, ldd, b.d, n, n, n, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     return PMP_OK;
 }
