@@ -74,14 +74,16 @@ __device__ __forceinline__ uint32_t row_scan_incl(uint32_t v)
     return v;
 }
 
-// Sum over the 16 lanes of each row (xor butterflies stay inside a row).
+// Sum over the 16 lanes of each row, in every lane (DPP row rotations: no LDS
+// round trips, of which a butterfly of permutes waits for four in a row).
 __device__ __forceinline__ unsigned long long row_sum(unsigned long long v)
 {
-    v += __shfl_xor(v, 8);
-    v += __shfl_xor(v, 4);
-    v += __shfl_xor(v, 2);
-    v += __shfl_xor(v, 1);
-    return v;
+    uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+    dpp_add64<0x128, 0xF>(lo, hi);  // row_ror:8
+    dpp_add64<0x124, 0xF>(lo, hi);  // row_ror:4
+    dpp_add64<0x122, 0xF>(lo, hi);  // row_ror:2
+    dpp_add64<0x121, 0xF>(lo, hi);  // row_ror:1
+    return ((unsigned long long)hi << 32) | lo;
 }
 
 template <int WD, bool H>
