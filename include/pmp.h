@@ -378,7 +378,8 @@ PMP_API pmp_status pmp_ga_autotune(pmp_ga *ga, int32_t *clients, int32_t *waves,
  *                   timing it: every run keeps its own tuned clients per
  *                   workgroup (scaled to the batch kernel's 16 waves) unless
  *                   one common count of clients per workgroup (64 ... 512;
- *                   more for a run whose partial sums would not fit) is
+ *                   fewer for a run whose walks are longer, more for one
+ *                   whose partial sums would not fit) is
  *                   faster over the whole batch; the choice goes to
  *                   `*clients` (optional; 0 = each run's own).  The probe
  *                   evaluates each run's generation-0

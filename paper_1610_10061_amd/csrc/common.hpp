@@ -346,6 +346,10 @@ struct BatchArgs {
     const int32_t *group0;  // ... of groups
     // the run of every chromosome, evaluation tile and group of the batch
     const int32_t *chrom_run, *tile_run, *group_run;
+    // the batch evaluation's workgroups: XCD x's k-th takes tile .y of run .x
+    // given at place[x * place_len + k] (.x < 0: none)
+    const int2 *place;
+    int32_t place_len;
     int32_t count, max_S;
     uint32_t *bar;          // grid barrier: epoch word, then one flag per
                             // workgroup (32 words apart)
@@ -366,11 +370,11 @@ struct BatchEvents {
     int *used = nullptr;
 };
 // The same generations as a sequence of batch-wide kernels (one per phase).
-hipError_t launch_ga_batch_kernels(const BatchArgs &b, int nchrom, int ntiles,
-                                   int ngroups, int generations, int max_w2,
+hipError_t launch_ga_batch_kernels(const BatchArgs &b, int nchrom, int ngroups,
+                                   int generations, int max_w2,
                                    hipStream_t s, const BatchEvents &ev = BatchEvents{});
 // One batch-wide evaluation of every run's current population (buffer 0),
 // as the first evaluation of a generation does (the batch autotuner's probe).
-hipError_t launch_ga_batch_eval(const BatchArgs &b, int ntiles, int max_w2, hipStream_t s);
+hipError_t launch_ga_batch_eval(const BatchArgs &b, int max_w2, hipStream_t s);
 
 }  // namespace pmp

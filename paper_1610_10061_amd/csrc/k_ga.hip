@@ -522,21 +522,18 @@ __global__ __launch_bounds__(kEvalTile *kBatchEvalWaves)
 {
     __shared__ __align__(16) uint32_t smask[eval_stage_words<WD>()];
     __shared__ unsigned long long sred[2 * kBatchEvalWaves * kEvalTile];
-    const int ntiles = B.tile0[B.count];
-    // blocks are dealt to the 8 XCDs round-robin: give XCD x a contiguous
-    // eighth of the tile range
-    const int per_xcd = (int)gridDim.x >> 3;
-    const int item = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
-    if (item >= ntiles)
+    // blocks are dealt to the 8 XCDs round-robin; the host has given each
+    // XCD's workgroups their tiles, the longest first
+    const int2 at = B.place[((int)blockIdx.x & 7) * B.place_len + ((int)blockIdx.x >> 3)];
+    if (at.x < 0)
         return;
-    const int b = B.tile_run[item];
+    const int b = at.x, local = at.y;
     const BatchItem &it = B.items[b];
     if (ga_stopped(it.g) || k >= it.S)
         return;
     EvalArgs e = it.e;
     e.masks = buf ? it.g.off[1] : it.g.off[0];
     e.active = buf ? it.g.ok[1] : it.g.ok[0];
-    const int local = item - B.tile0[b];
     const int ti = local / e.tiles_c;
     // the walk each instance's scan lengths call for (uniform per workgroup)
     if (e.paired)
@@ -586,11 +583,11 @@ __global__ __launch_bounds__(256) void k_batch_best(BatchArgs B)
 }
 
 template <int WD>
-hipError_t batch_kernels_wd(const BatchArgs &b, int nchrom, int ntiles, int ngroups,
-                            int generations, hipStream_t s, const BatchEvents &ev)
+hipError_t batch_kernels_wd(const BatchArgs &b, int nchrom, int ngroups, int generations,
+                            hipStream_t s, const BatchEvents &ev)
 {
     const dim3 waves((unsigned)((nchrom + kGaWaves - 1) / kGaWaves));
-    const dim3 tiles((unsigned)(((ntiles + 7) / 8) * 8));
+    const dim3 tiles((unsigned)(8 * b.place_len));
     // the evaluation launch, bracketed by the next pair of events if any
     auto eval = [&](int k, int buf) {
         if (ev.events && *ev.used + 2 <= ev.cap) {
@@ -799,14 +796,14 @@ hipError_t launch_ga_resolve_init(const GaArgs &g, int in, int out, hipStream_t 
     return hipGetLastError();
 }
 
-hipError_t launch_ga_batch_kernels(const BatchArgs &b, int nchrom, int ntiles,
-                                   int ngroups, int generations, int max_w2,
-                                   hipStream_t s, const BatchEvents &ev)
+hipError_t launch_ga_batch_kernels(const BatchArgs &b, int nchrom, int ngroups,
+                                   int generations, int max_w2, hipStream_t s,
+                                   const BatchEvents &ev)
 {
     const int w2 = max_w2;
 #define PMP_BATCH_KWD(N)                                                       \
     if (w2 <= N)                                                               \
-        return batch_kernels_wd<N>(b, nchrom, ntiles, ngroups, generations, s, ev);
+        return batch_kernels_wd<N>(b, nchrom, ngroups, generations, s, ev);
     PMP_BATCH_KWD(2)
     PMP_BATCH_KWD(4)
     PMP_BATCH_KWD(8)
@@ -824,19 +821,19 @@ hipError_t launch_ga_batch_kernels(const BatchArgs &b, int nchrom, int ntiles,
 }
 
 template <int WD>
-hipError_t batch_eval_wd(const BatchArgs &b, int ntiles, hipStream_t s)
+hipError_t batch_eval_wd(const BatchArgs &b, hipStream_t s)
 {
-    const dim3 tiles((unsigned)(((ntiles + 7) / 8) * 8));
+    const dim3 tiles((unsigned)(8 * b.place_len));
     hipLaunchKernelGGL(k_batch_eval<WD>, tiles, dim3(kEvalTile * kBatchEvalWaves), 0, s, b, -1,
                        0);
     return hipGetLastError();
 }
 
-hipError_t launch_ga_batch_eval(const BatchArgs &b, int ntiles, int max_w2, hipStream_t s)
+hipError_t launch_ga_batch_eval(const BatchArgs &b, int max_w2, hipStream_t s)
 {
 #define PMP_BATCH_EWD(N)                                                       \
     if (max_w2 <= N)                                                           \
-        return batch_eval_wd<N>(b, ntiles, s);
+        return batch_eval_wd<N>(b, s);
     PMP_BATCH_EWD(2)
     PMP_BATCH_EWD(4)
     PMP_BATCH_EWD(8)

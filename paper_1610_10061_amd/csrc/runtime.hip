@@ -482,6 +482,10 @@ struct BatchHost {
     std::vector<int32_t> runs;
     int32_t *d_runs = nullptr;
     int max_tiles = 0;
+    // the evaluation's workgroups in launch order (BatchArgs::place)
+    std::vector<int2> place;
+    int2 *d_place = nullptr;
+    size_t place_cap = 0;
 
     void drop_graphs()
     {
@@ -497,6 +501,8 @@ struct BatchHost {
         dfree(d_items);
         dfree(d_prefix);
         dfree(d_runs);
+        dfree(d_place);
+        place_cap = 0;
         dfree(d_bar);
         dfree(d_err);
     }
@@ -788,13 +794,66 @@ namespace {
 
 EvalArgs ga_eval_args(const pmp_ga *ga, const GaArgs &g, int buf);
 
+// What a client of a run costs a wave of the batch evaluation, relative to one
+// whose walk ends in its first 64-entry chunk: the walk goes on to the longest
+// of its 64 chromosomes' scans, about (ln 64 + 0.58) m / p entries, and a
+// further chunk costs half a first one.
+double client_cost(const pmp_instance *inst)
+{
+    const double longest = std::min((double)inst->K, 4.74 * inst->m / inst->p);
+    return 1.0 + 0.5 * (std::ceil(longest / 64.0) - 1.0);
+}
+
+// The evaluation's workgroups in launch order: units of one client tile (its
+// chromosome tiles side by side, on one XCD, sharing the rows in its L2),
+// longest first, each to the XCD with the least work so far, so that the
+// launch does not end with a long workgroup that started late.
+void batch_place(BatchHost &bh)
+{
+    struct Unit {
+        double cost;
+        int run, ti;
+    };
+    std::vector<Unit> units;
+    for (int b = 0; b < (int)bh.items.size(); ++b) {
+        const EvalArgs &e = bh.items[b].e;
+        const double per = client_cost(bh.gas[b]->inst);
+        for (int ti = 0; ti < e.tiles_i; ++ti) {
+            const int clients = std::min(e.clients_per_block, e.t.n - ti * e.clients_per_block);
+            // (64: what staging a workgroup's tile costs, in clients)
+            units.push_back({64.0 + per * clients, b, ti});
+        }
+    }
+    std::stable_sort(units.begin(), units.end(),
+                     [](const Unit &x, const Unit &y) { return x.cost > y.cost; });
+    std::vector<int2> list[8];
+    double load[8] = {0};
+    size_t len = 1;
+    for (const Unit &u : units) {
+        const int x = (int)(std::min_element(load, load + 8) - load);
+        const int tiles_c = bh.items[u.run].e.tiles_c;
+        load[x] += u.cost * tiles_c;
+        for (int tc = 0; tc < tiles_c; ++tc)
+            list[x].push_back(make_int2(u.run, u.ti * tiles_c + tc));
+        len = std::max(len, list[x].size());
+    }
+    bh.place.assign(8 * len, make_int2(-1, 0));
+    for (int x = 0; x < 8; ++x)
+        std::copy(list[x].begin(), list[x].end(), bh.place.begin() + x * len);
+    bh.args.place_len = (int32_t)len;
+}
+
 // The batch's client tiling: with clients = 0 every run keeps its own
-// tuning (base_cpb), else every run takes `clients` clients per evaluation
-// workgroup, or more where its partial-sum buffers (sized for the larger of
-// its own and its fused launches' tile counts) hold fewer tiles than that
-// gives; the stage steps read the partial sums with the same tiling.
-// Uploads the run table and prefix offsets; graphs captured for another
-// tiling are dropped.
+// tuning (base_cpb), else a run takes `clients` clients per evaluation
+// workgroup divided by what a client of it costs, so that workgroups last
+// about as long (at 192 clients each, the ones of a run with n = 2000, p = 5
+// walked fifteen times as many chunks as most and set the launch's time), or
+// more where its partial-sum buffers (sized for the larger of its own and its
+// fused launches' tile counts) hold fewer tiles than that gives; the stage
+// steps read the partial sums with the same tiling.
+// Uploads the run table, prefix offsets and launch order; graphs captured for
+// another tiling are dropped.  64 ragged instances, 20 generations: 24.2 ms with
+// the same clients for every run, 20.3 ms (best common counts 192 and 384).
 hipError_t batch_tiles(BatchHost &bh, int clients)
 {
     const int count = (int)bh.gas.size();
@@ -803,8 +862,13 @@ hipError_t batch_tiles(BatchHost &bh, int clients)
         BatchItem &it = bh.items[b];
         const pmp_ga *ga = bh.gas[b];
         const int n = ga->inst->n, cap = std::max(ga->TI, ga->fTI);
-        it.e.clients_per_block =
-            clients > 0 ? std::max(clients, (n + cap - 1) / cap) : bh.base_cpb[b];
+        if (clients > 0) {
+            const double cost = client_cost(ga->inst);
+            const int own = cost > 1.0 ? std::max(16, (int)(clients / cost) / 16 * 16) : clients;
+            it.e.clients_per_block = std::max(own, (n + cap - 1) / cap);
+        } else {
+            it.e.clients_per_block = bh.base_cpb[b];
+        }
         it.e.tiles_i = (bh.gas[b]->inst->n + it.e.clients_per_block - 1) / it.e.clients_per_block;
         it.g.TI = it.e.tiles_i;
         t0[b + 1] = t0[b] + it.e.tiles_c * it.e.tiles_i;
@@ -814,7 +878,19 @@ hipError_t batch_tiles(BatchHost &bh, int clients)
         for (int x = t0[b]; x < t0[b + 1]; ++x)
             tile_run[x] = b;
     bh.drop_graphs();
-    hipError_t e = hipMemcpy(bh.d_items, bh.items.data(), sizeof(BatchItem) * count,
+    batch_place(bh);
+    if (bh.place_cap < bh.place.size()) {
+        dfree(bh.d_place);
+        bh.place_cap = 0;
+        if (dalloc(&bh.d_place, bh.place.size()) != hipSuccess)
+            return hipErrorOutOfMemory;
+        bh.place_cap = bh.place.size();
+    }
+    bh.args.place = bh.d_place;
+    hipError_t e = hipMemcpy(bh.d_place, bh.place.data(), sizeof(int2) * bh.place.size(),
+                             hipMemcpyHostToDevice);
+    if (e == hipSuccess)
+        e = hipMemcpy(bh.d_items, bh.items.data(), sizeof(BatchItem) * count,
                              hipMemcpyHostToDevice);
     if (e == hipSuccess)
         e = hipMemcpy(bh.d_prefix, bh.prefix.data(), sizeof(int32_t) * bh.prefix.size(),
@@ -938,7 +1014,7 @@ hipError_t batch_enqueue(pmp_batch *bt, int generations, hipStream_t s, bool coo
         ev.cap = (int)bt->ev.size();
         ev.used = &bt->ev_used;
     }
-    return launch_ga_batch_kernels(bh.args, bh.nchrom, bh.ntiles, bh.ngroups, generations,
+    return launch_ga_batch_kernels(bh.args, bh.nchrom, bh.ngroups, generations,
                                    bh.max_w2, s, ev);
 }
 
@@ -2561,12 +2637,12 @@ pmp_status pmp_batch_autotune(pmp_batch *bt, int32_t *clients, void *stream)
         if (e == hipSuccess)
             e = batch_tiles(bh, common);
         if (e == hipSuccess)
-            e = launch_ga_batch_eval(bh.args, bh.ntiles, bh.max_w2, s);  // warm-up
+            e = launch_ga_batch_eval(bh.args, bh.max_w2, s);  // warm-up
         float least = 1e30f;
         for (int trial = 0; trial < 3 && e == hipSuccess; ++trial) {
             e = hipEventRecord(e0, s);
             for (int rep = 0; rep < 4 && e == hipSuccess; ++rep)
-                e = launch_ga_batch_eval(bh.args, bh.ntiles, bh.max_w2, s);
+                e = launch_ga_batch_eval(bh.args, bh.max_w2, s);
             if (e == hipSuccess)
                 e = hipEventRecord(e1, s);
             if (e == hipSuccess)
