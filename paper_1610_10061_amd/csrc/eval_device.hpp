@@ -7,16 +7,17 @@
 // clients, exact in 64-bit integers.
 //
 // Mapping (gfx950, wave64).  A workgroup owns a tile of 64 chromosomes and
-// a tile of clients; each of its four waves takes every fourth client of the
-// tile.  The tile's masks are staged in LDS and turned facility-major once:
+// a tile of clients; each of its NV waves (16 mostly) takes every NV-th client
+// of the tile.  The tile's masks are staged in LDS and turned facility-major once:
 // T[j] is a 64-bit word whose bit c says whether facility j is open in
 // chromosome c (a 64 x 64 bit transpose per 64 facilities).  For one client
 // the wave loads 64 consecutive entries of Pi'_i and D'_i, one per lane
 // (coalesced), and every lane reads T of the facility at its position: lane
 // k then holds row k of the 64 x 64 bit matrix "position k is open in
-// chromosome c".  One more transpose in registers (lane exchanges and bit
-// selects, about 35 instructions) gives lane c its column, and the column's
-// lowest set bit is chromosome c's first open position in this chunk.  One
+// chromosome c".  One more transpose (half of it done by the LDS read itself
+// where that pays, first_open_lds, the rest by lane exchanges and bit
+// selects) gives lane c its column, and the column's lowest set bit is
+// chromosome c's first open position in this chunk.  One
 // ds_bpermute then fetches each chromosome's D' entry from the lane that
 // holds it (the lane is bits 7:2 of its address, so position -1 needs no
 // mask: lanes without a hit discard the value), so a chunk costs the same for
@@ -145,6 +146,77 @@ __device__ __forceinline__ int first_open(uint64_t row, int lane, const Transpos
     // v_ffbl gives 0xFFFFFFFF for a zero word: the unsigned minimum of the
     // low word's position and 32 plus the high word's (saturating, so that
     // "none" stays 0xFFFFFFFF) is the first open position, or -1
+    const uint32_t a = (uint32_t)lowest_bit(lo);
+    const uint32_t b = __builtin_elementwise_add_sat((uint32_t)lowest_bit(hi), 32u);
+    return (int)(a < b ? a : b);
+}
+
+// The chromosome in bit q of a facility-major word that first_open_lds reads
+// (its own inverse: q's halves exchanged).
+__device__ __forceinline__ int tile_bit(int q)
+{
+    return ((q & 7) << 3) | (q >> 3);
+}
+
+// Per-lane operands of first_open_lds.
+struct ChunkLanes {
+    uint32_t keep, rot;  // step C: the bits a lane keeps, its partner's rotation
+    int pos;             // position of the chunk whose facility the lane reads
+
+    __device__ __forceinline__ explicit ChunkLanes(int lane)
+    {
+        const bool up = (lane & 8) != 0;
+        keep = up ? 0xAAAAAAAAu : 0x55555555u;
+        rot = up ? 1u : 31u;
+        const int b0 = lane & 1, b1 = (lane >> 1) & 1, b2 = (lane >> 2) & 1;
+        const int b3 = (lane >> 3) & 1, b4 = (lane >> 4) & 1, b5 = lane >> 5;
+        pos = b4 << 5 | b2 << 4 | b1 << 3 | b3 << 2 | b5 << 1 | b0;
+    }
+};
+
+// first_open on facility-major words in LDS whose bit q is chromosome
+// tile_bit(q): every lane reads the word of its facility j, and lane c gets
+// chromosome c's first open position.  gfx950's transposing LDS read
+// (ds_read_b64_tr_b8) returns to lane 16 g + 8 r + c the bytes c of the words
+// that lanes 16 g + 2 t + r read, t = 0..7 (found by a test of every lane and
+// byte): three of the six exchanges of a lane bit with a bit index come with
+// the read itself.  With lane bits (g1 g0 r c2 c1 c0) and bit index (t2 t1 t0
+// b2 b1 b0) - c, b the chromosome's byte and bit - the others are
+//  A: t2 with b2 within the lane's two words, then the word with lane bit 5
+//     (v_permlane32_swap);
+//  B: the same with b1, lane bit 4 and v_permlane16_swap;
+//  C: b0 with lane bit 3 by a row rotation.
+// Lane (b2 b1 b0 c2 c1 c0) then holds bit index (g0 t1 t0 t2 g1 r), so lanes
+// take their facility from position ChunkLanes::pos and the lowest set bit is
+// the first open position.  Two LDS accesses and 27 VALU instructions a
+// chunk, with the distance's fetch, against 8 (three of them one after
+// another) and 40 with every exchange between lanes: m = 3333, p = 333, 4801
+// clients x 4001 chromosomes 37 -> 31 us, n = m = 5000, p = 500 36.1 -> 32.4 us.
+__device__ __forceinline__ int first_open_lds(const uint64_t *sT, uint32_t j,
+                                              const ChunkLanes &cl)
+{
+    typedef int v2i __attribute__((ext_vector_type(2)));
+    typedef __attribute__((address_space(3))) v2i lds_v2i;
+    const v2i w = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i *)(sT + j));
+    uint32_t lo = (uint32_t)w.x, hi = (uint32_t)w.y;
+    {
+        const uint32_t a = bit_select(0x0F0F0F0Fu, lo, hi << 4);
+        const uint32_t b = bit_select(0x0F0F0F0Fu, lo >> 4, hi);
+        const auto sw = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+        lo = (uint32_t)sw[0];
+        hi = (uint32_t)sw[1];
+    }
+    {
+        const uint32_t a = bit_select(0x33333333u, lo, hi << 2);
+        const uint32_t b = bit_select(0x33333333u, lo >> 2, hi);
+        const auto sw = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+        lo = (uint32_t)sw[0];
+        hi = (uint32_t)sw[1];
+    }
+    const uint32_t ylo = (uint32_t)__builtin_amdgcn_mov_dpp((int)lo, 0x128, 0xF, 0xF, true);
+    const uint32_t yhi = (uint32_t)__builtin_amdgcn_mov_dpp((int)hi, 0x128, 0xF, 0xF, true);
+    lo = bit_select(cl.keep, lo, __builtin_amdgcn_alignbit(ylo, ylo, cl.rot));
+    hi = bit_select(cl.keep, hi, __builtin_amdgcn_alignbit(yhi, yhi, cl.rot));
     const uint32_t a = (uint32_t)lowest_bit(lo);
     const uint32_t b = __builtin_elementwise_add_sat((uint32_t)lowest_bit(hi), 32u);
     return (int)(a < b ? a : b);
@@ -288,37 +360,46 @@ constexpr int eval_stage_words()
 // stride WD + 1, zero past 2W words) and the chromosomes' active flags in
 // sact, and synchronised the workgroup (the stage steps fused with the
 // evaluation make the offspring right there).
-// Clients whose first 64-entry chunk a wave of the single-client walk has
-// in flight (loaded up to this many clients ahead, so that the wait for a
-// client's chunk falls several clients' work after its load).
-constexpr int kPrefetch = 4;
+// Whether the single-client walk reads its first chunks by first_open_lds.
+// Not for chromosomes of up to four words: their few facilities send most
+// clients on to a second chunk, and handing over between the two numberings
+// of the lanes costs more than the read saves (a GA generation at n = 100: 57.0
+// us without, 59.1 with; n = 400 the same; n = 900 103.8 and 102.9).
+template <int WD>
+constexpr bool eval_reads_transposed(bool R, bool H, bool GT)
+{
+    return !R && !H && !GT && WD > 8;
+}
 
-// The first chunks (Pi' entry and D' value of this lane's position) of the
-// first clients a lane's wave walks in client tile ti: kPrefetch clients for
-// the single-client walk, one pair for the paired walk (H: lanes 32-63 hold
-// the pair's second client).  Always in bounds: rows clamped into the tile,
-// columns below K.
-struct FirstChunks {
-    uint32_t j[kPrefetch];
-    int32_t d[kPrefetch];
+// The first chunk (Pi' entry and D' value of this lane's position) of the
+// first client, or pair of clients (H: lanes 32-63 hold the second), that a
+// lane's wave walks in client tile ti.  Always in bounds: rows clamped into
+// the tile, columns below K.  TR: the Pi' entry is the one first_open_lds
+// wants of the lane.
+struct FirstChunk {
+    uint32_t j;
+    int32_t d;
 };
 
-template <bool H, int NV>
-__device__ __forceinline__ void eval_first_chunks(const EvalArgs &a, int ti, int lane, int wave,
-                                                  FirstChunks &fc)
+template <bool H, int NV, bool TR>
+__device__ __forceinline__ FirstChunk eval_first_chunk(const EvalArgs &a, int ti, int lane,
+                                                       int wave)
 {
     const int i0 = ti * a.clients_per_block;
     const int i1 = min(a.t.n, i0 + a.clients_per_block);
     const int i = i0 + wave, last = i1 - 1;
-    const int pos = H ? (lane & 31) : lane;
-    const int col = pos < a.t.K ? pos : a.t.K - 1;
-    constexpr int Q = H ? 1 : kPrefetch;
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        const int row = (H && lane >= 32) ? min(i + NV, last) : min(i + NV * q, last);
-        fc.j[q] = a.t.pi[(int64_t)row * a.t.pitch + col];
-        fc.d[q] = a.t.ds[(int64_t)row * a.t.pitch + col];
+    FirstChunk fc;
+    if constexpr (H) {
+        const int col = min(lane & 31, a.t.K - 1);
+        const int64_t row = (int64_t)min(lane >= 32 ? i + NV : i, last) * a.t.pitch;
+        fc.j = a.t.pi[row + col];
+        fc.d = a.t.ds[row + col];
+    } else {  // (a row is the wave's: scalar base, 32-bit lane offset)
+        const int64_t row = (int64_t)min(i, last) * a.t.pitch;
+        fc.j = (a.t.pi + row)[(uint32_t)min(TR ? ChunkLanes(lane).pos : lane, a.t.K - 1)];
+        fc.d = (a.t.ds + row)[(uint32_t)min(lane, a.t.K - 1)];
     }
+    return fc;
 }
 
 //
@@ -337,10 +418,12 @@ __device__ __forceinline__ void eval_tile(const EvalArgs &a, int ti, int tc,
                                           uint32_t *smask,
                                           unsigned long long *sred,
                                           const uint8_t *sact = nullptr,
-                                          const FirstChunks *pre = nullptr,
+                                          const FirstChunk *pre = nullptr,
                                           bool live = true)
 {
     constexpr int SD = WD + 1;  // staged row stride
+    // single-client walk on facility-major words in LDS: first_open_lds
+    constexpr bool TR = eval_reads_transposed<WD>(R, H, GT);
     const int c0 = tc * kEvalTile;
     const int i0 = ti * a.clients_per_block;
     const int i1 = min(a.t.n, i0 + a.clients_per_block);
@@ -364,36 +447,23 @@ __device__ __forceinline__ void eval_tile(const EvalArgs &a, int ti, int tc,
     const int col = pos < a.t.K ? pos : a.t.K - 1;
     const bool in_row = pos < a.t.K;
     const int last = i1 - 1;
-    const int row_first = (H && lane >= 32) ? min(i + NV, last) : min(i, last);
-    // queue of the next clients' first chunks (the single-client walk keeps
-    // kPrefetch in flight; the reduced and paired walks one)
-    constexpr int PF = (!H && !R) ? kPrefetch : 1;
-    uint32_t jq[PF];
-    int32_t dq[PF];
+    uint32_t j_cur;
+    int32_t d_cur = 0;
     long long e_cur = 0;
     int k_cur = 0;  // R: the row's length K_i
-    if constexpr (PRE) {  // loaded by the caller (eval_first_chunks)
-#pragma unroll
-        for (int q = 0; q < PF; ++q) {
-            jq[q] = pre->j[q];
-            dq[q] = pre->d[q];
-        }
-    } else if constexpr (R) {
-        jq[0] = a.t.pi[(int64_t)row_first * a.t.pitch + col];
-        dq[0] = 0;
+    if constexpr (R) {
+        j_cur = a.t.pi[(int64_t)min(i, last) * a.t.pitch + col];
         e_cur = a.e64[(int64_t)min(i, last) * a.t.pitch + col];
         k_cur = a.rlen[min(i, last)];
     } else {
-        FirstChunks fc;
-        eval_first_chunks<H, NV>(a, ti, lane, wave, fc);
-#pragma unroll
-        for (int q = 0; q < PF; ++q) {
-            jq[q] = fc.j[q];
-            dq[q] = fc.d[q];
-        }
+        FirstChunk fc;
+        if constexpr (PRE)  // loaded by the caller
+            fc = *pre;
+        else
+            fc = eval_first_chunk<H, NV, TR>(a, ti, lane, wave);
+        j_cur = fc.j;
+        d_cur = fc.d;
     }
-    uint32_t j_cur = jq[0];
-    int32_t d_cur = dq[0];
     // Masks: every load unconditional at a clamped (always valid) address,
     // in batches, so that a batch costs one round trip; out-of-range words
     // are replaced by 0 when stored.
@@ -448,6 +518,11 @@ __device__ __forceinline__ void eval_tile(const EvalArgs &a, int ti, int tc,
     const uint64_t *sT = nullptr;
     const uint32_t jz = (uint32_t)(64 * W), jone = jz + 1u;
     const TransposeLanes tl(lane);
+    // chromosome of this lane's bit of the facility-major words, and the
+    // active chromosomes as such bits (the walk past the first chunk keeps
+    // lane q for bit q)
+    const int cq = TR ? tile_bit(lane) : lane;
+    const uint64_t act_q = TR ? __builtin_amdgcn_ballot_w64(((act >> cq) & 1ull) != 0ull) : act;
     if constexpr (GT) {
         sT = a.tg + (int64_t)tc * a.tg_stride;
     } else {
@@ -456,10 +531,10 @@ __device__ __forceinline__ void eval_tile(const EvalArgs &a, int ti, int tc,
 #pragma unroll
         for (int r = 0; r < NW; ++r) {
             const int w = min(wave + r * NV, W - 1);
-            rlo[r] = smask[lane * SD + 2 * w];
-            rhi[r] = smask[lane * SD + 2 * w + 1];
+            rlo[r] = smask[cq * SD + 2 * w];
+            rhi[r] = smask[cq * SD + 2 * w + 1];
         }
-        // Feasibility of each chromosome (lane), checked once (first client
+        // Feasibility of each chromosome (lane cq), checked once (first client
         // tile) from the rows just read: each wave counts the open facilities in
         // its words and looks for bits past m in the last word; wave 0 adds the
         // waves' counts up once the copy's barrier has passed.
@@ -496,7 +571,7 @@ __device__ __forceinline__ void eval_tile(const EvalArgs &a, int ti, int tc,
         if (wave == 0 && lane < 2)
             sTw[jz + lane] = lane ? ~0ull : 0ull;
         __syncthreads();
-        if (ti == 0 && wave == 0 && my_act) {
+        if (ti == 0 && wave == 0 && ((act_q >> lane) & 1ull)) {
             uint32_t ones = 0, stray = 0;
 #pragma unroll
             for (int v = 0; v < NV; ++v) {
@@ -548,44 +623,61 @@ __device__ __forceinline__ void eval_tile(const EvalArgs &a, int ti, int tc,
             d_cur = d_nxt;
         }
     }
-    for (; !H && i < i1; i += NV) {
-        j_cur = jq[0];
-        d_cur = dq[0];
-        // refill the queue: the client PF places ahead
-#pragma unroll
-        for (int q = 0; q + 1 < PF; ++q) {
-            jq[q] = jq[q + 1];
-            dq[q] = dq[q + 1];
+    // costs and scan lengths of the walks past the first chunk, by bit of the
+    // facility-major words
+    unsigned long long acc_q = 0;
+    uint32_t scn_q = 0;
+    const ChunkLanes cl(lane);
+    const int jcol = TR ? min(cl.pos, a.t.K - 1) : col;
+    for (; !H && !R && i < i1; i += NV) {
+        // (one chunk ahead: with four in flight the moves between their
+        // registers and a third of a workgroup's occupancy cost more than the
+        // loads' latency - n = 900, P = 1024: 103.5 us a generation with four,
+        // 100.3 with one; n = m = 5000, p = 10: 503 and 508 us an evaluation)
+        const int64_t next = (int64_t)min(i + NV, last) * a.t.pitch;
+        const uint32_t j_nxt = (a.t.pi + next)[(uint32_t)jcol];
+        const int32_t d_nxt = (a.t.ds + next)[(uint32_t)col];
+        // The first chunk by a transpose (most chromosomes stop in it), the
+        // others in walk_rest.  A lane past the row's end holds the last entry
+        // again: the same facility at a later place, which no first open
+        // position can be.  A lane without a hit has hit = -1 and adds 0 to the
+        // scan length; lanes of inactive chromosomes add what they like.
+        const int hit = TR ? first_open_lds(sT, j_cur, cl) : first_open(sT[j_cur], lane, tl);
+        const int32_t cost = __builtin_amdgcn_ds_bpermute(hit << 2, d_cur);
+        acc += hit >= 0 ? (uint32_t)cost : 0u;
+        scn += (uint32_t)(hit + 1);
+        if ((act & ~__builtin_amdgcn_ballot_w64(hit >= 0)) != 0ull) {
+            const int hq = TR ? __builtin_amdgcn_ds_bpermute(cq << 2, hit) : hit;
+            const uint64_t pend = act_q & ~__builtin_amdgcn_ballot_w64(hq >= 0);
+            const int64_t row = (int64_t)i * a.t.pitch;
+            walk_rest(a, a.t.pi + row, a.t.ds + row, 64, pend, lane, sT, jz, tl, acc_q, scn_q,
+                      late);
         }
-        const int inext = min(i + NV * PF, last);
-        jq[PF - 1] = a.t.pi[(int64_t)inext * a.t.pitch + col];
-        long long e_nxt = 0;
-        int k_nxt = 0;
-        if (R) {
-            e_nxt = a.e64[(int64_t)inext * a.t.pitch + col];
-            k_nxt = a.rlen[inext];
-        } else {
-            dq[PF - 1] = a.t.ds[(int64_t)inext * a.t.pitch + col];
+        j_cur = j_nxt;
+        d_cur = d_nxt;
+    }
+    if constexpr (!H && !R) {
+        late.add_to(acc_q);
+        late = LateCosts{};
+        if constexpr (TR) {  // to the lanes of their chromosomes
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(cq << 2, (int)(uint32_t)acc_q);
+            const uint32_t hi =
+                (uint32_t)__builtin_amdgcn_ds_bpermute(cq << 2, (int)(uint32_t)(acc_q >> 32));
+            acc_q = ((unsigned long long)hi << 32) | lo;
+            scn_q = (uint32_t)__builtin_amdgcn_ds_bpermute(cq << 2, (int)scn_q);
         }
+        acc += acc_q;
+        scn += scn_q;
+    }
+    for (; R && i < i1; i += NV) {
+        const int inext = min(i + NV, last);
+        const uint32_t j_nxt = a.t.pi[(int64_t)inext * a.t.pitch + col];
+        const long long e_nxt = a.e64[(int64_t)inext * a.t.pitch + col];
+        const int k_nxt = a.rlen[inext];
         const uint16_t *prow = a.t.pi + (int64_t)i * a.t.pitch;
-        const int32_t *drow = a.t.ds + (int64_t)i * a.t.pitch;
-        const long long *erow = R ? a.e64 + (int64_t)i * a.t.pitch : nullptr;
+        const long long *erow = a.e64 + (int64_t)i * a.t.pitch;
         uint64_t pend = act;
-        if constexpr (!R) {
-            // the first chunk (by a transpose: most chromosomes stop in it),
-            // the others in walk_rest
-            const int hit = first_open(sT[in_row ? j_cur : jz], lane, tl);
-            const bool found = ((pend >> lane) & 1ull) && hit >= 0;
-            const int32_t cost = __builtin_amdgcn_ds_bpermute(hit << 2, d_cur);
-            if (found) {
-                acc += (uint32_t)cost;
-                scn += (uint32_t)(hit + 1);
-            }
-            pend &= ~__builtin_amdgcn_ballot_w64(hit >= 0);  // as in walk_rest
-            if (pend != 0ull)
-                walk_rest(a, prow, drow, 64, pend, lane, sT, jz, tl, acc, scn, late);
-        }
-        for (int base = 0; R && pend != 0ull; base += 64) {
+        for (int base = 0; pend != 0ull; base += 64) {
             if (base >= a.t.K) {  // fewer than p open facilities
                 if (lane == 0)
                     atomicOr(a.err, ERR_SCAN_OVERRUN);
@@ -619,6 +711,7 @@ __device__ __forceinline__ void eval_tile(const EvalArgs &a, int ti, int tc,
             }
             pend &= ~__builtin_amdgcn_ballot_w64(hit >= 0);  // as in walk_rest
         }
+        j_cur = j_nxt;
         e_cur = e_nxt;
         k_cur = k_nxt;
     }

@@ -154,8 +154,9 @@ __global__ __launch_bounds__(kEvalTile *kFusedWaves) void k_stage_eval(GaArgs g,
         h2 = ph & keep;
         sc2 = ps & keep;
     }
-    FirstChunks fc;
-    eval_first_chunks<H, kFusedWaves>(a, ti, lane, wave, fc);
+    const FirstChunk fc =
+        eval_first_chunk<H, kFusedWaves, eval_reads_transposed<WD>(false, H, false)>(a, ti, lane,
+                                                                                     wave);
     // client tiles past 32 (small populations of many clients)
     for (int t = w + 32; t < g.TI; t += 16) {
         f2 += g.part[t * ts + c * xs];

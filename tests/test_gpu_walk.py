@@ -66,3 +66,22 @@ def test_no_open_facility_is_reported(pm, m, p):
     assert err.value.status == 4
     np.testing.assert_array_equal(fit[:65],
                                   oracle.objective(gi.euclid_instance(m, 1), masks[:65], p))
+
+
+@pytest.mark.parametrize("m,p", [(255, 20), (256, 20), (257, 20), (320, 3), (1000, 100)])
+@pytest.mark.parametrize("waves,P", [(4, 1), (8, 37), (16, 64), (16, 100)])
+def test_both_chunk_reads(pm, monkeypatch, m, p, waves, P):
+    """Chromosomes of four words and of five (the transposing read of the
+    first chunk starts there), partly filled tiles, each wave count."""
+    monkeypatch.setenv("PMP_EVAL_WAVES", str(waves))
+    rng = np.random.default_rng([m, p, P])
+    d = rng.integers(0, 2**31 - 1, size=(45, m)).astype(np.int32)
+    _compare(pm, d, p, gi.random_population(P, m, p, seed=P))
+
+
+@pytest.mark.parametrize("m,p", [(300, 238), (300, 237), (300, 280), (300, 299), (900, 895)])
+def test_rows_shorter_than_a_chunk(pm, monkeypatch, m, p):
+    """Rows of 2 to 64 entries through the single-client walk."""
+    monkeypatch.setenv("PMP_EVAL_PAIRED", "0")
+    d = np.random.default_rng([m, p]).integers(0, 50, size=(33, m)).astype(np.int32)
+    _compare(pm, d, p, gi.random_population(70, m, p, seed=p))
