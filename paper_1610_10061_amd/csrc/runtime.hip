@@ -636,8 +636,8 @@ struct pmp_ga {
         return spec_on && Y >= 2 && Y <= kMaxSpec;
     }
     // The mutants' evaluation covers Y times the population, so it takes
-    // larger client tiles than the population's (about 2048 workgroups):
-    // fewer partial sums for the resolve step to add up.
+    // larger client tiles than the population's: fewer workgroups to stage
+    // their chromosomes, fewer partial sums for the resolve step to add up.
     hipError_t ensure_spec()
     {
         const size_t PY = (size_t)prm.population * Y;
@@ -650,9 +650,18 @@ struct pmp_ga {
         }
         const long tiles_c = (long)((PY + kEvalTile - 1) / kEvalTile);
         const int n = inst->n;
-        const long target = std::max(1, env_int("PMP_MUTANT_WORKGROUPS", 1024));
+        // two workgroups per CU fill it (16 waves each); with fewer than 64
+        // mutant tiles one per CU, whose larger client tiles pay better for
+        // the staging than a second workgroup does for the waits.  A generation
+        // at n = 900, P = 1024: 100.4 us with 1024 workgroups, 97.8 with 512,
+        // 98.5 with 256; n = 900, P = 256: 85.2 with 512, 82.9 with 256; n = 2000,
+        // p = 20, P = 512 (64 tiles): 220 with 512, 242 with 256.
+        const long target =
+            std::max(1, env_int("PMP_MUTANT_WORKGROUPS", (tiles_c < 64 ? 1 : 2) * device_cus()));
         int ti = (int)std::max(1L, std::min((long)n, target / std::max(1L, tiles_c)));
-        ti = std::max(ti, (n + 127) / 128);  // at most 128 clients per workgroup
+        // at most 512 clients per workgroup (n = 5000: 286 us a generation with
+        // 128, 265 with 256, 251 with 512, 253 with 1024)
+        ti = std::max(ti, (n + 511) / 512);
         int cpb = (n + ti - 1) / ti;
         cpb = std::max(cpb, this->cpb);
         cpb = ((cpb + 3) / 4) * 4;
