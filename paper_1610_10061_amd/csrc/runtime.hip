@@ -236,9 +236,9 @@ int paired_scans(int m, int p)
 // Clients per workgroup of the evaluation kernel.  A workgroup first stages
 // its chromosome tile (W words per chromosome loaded and turned
 // facility-major), then walks its clients.  With long scans (mean
-// (m+1)/(p+1) of 128 entries or more) the walks dominate: enough workgroups
-// to fill 256 CUs four times over, at most 64 clients each, so that uneven
-// scan lengths even out.  With short scans the staging counts: the fewest
+// (m+1)/(p+1) of 128 entries or more) the walks dominate: whole rounds of the
+// resident slots, of few enough clients that uneven scan lengths even out.
+// With short scans the staging counts: the fewest
 // client tiles that still give every CU of the device about 2.75
 // workgroups, or that fill every CU's resident slots once when it holds
 // fewer than 3.5, so that no workgroup waits for a slot.
@@ -311,14 +311,23 @@ int clients_per_block(int n, int P, int m, int p, int W, bool reduced = false,
         return forced;
     const long tiles_c = (P + kEvalTile - 1) / kEvalTile;
     const bool long_scans = (long)m + 1 >= 128L * ((long)p + 1);
-    if (long_scans) {
-        long cpb = (long)n * tiles_c / 1024;
-        cpb = std::min(64L, std::max(4L, cpb));
-        return (int)(((cpb + waves - 1) / waves) * waves);
-    }
     const bool paired = paired_scans(m, p) != 0;
     const int cus = device_cus();
     const long slots = (long)cus * eval_workgroups_per_cu(W, reduced, paired, waves);
+    if (long_scans) {
+        // The fewest whole rounds of the chip's slots that leave a workgroup at
+        // most 160 clients.  Between whole rounds the last one is nearly empty:
+        // n = m = 5000, p = 10, P = 4096 500 us with 64 clients (10 rounds), 475
+        // with 160 (4), 499 with 192 (3.4); P = 1024 168, 156 and 185; n = m =
+        // 2000, p = 5, P = 4096 154 with the former 64, 151 with 128 (2 rounds).
+        const long unit = waves;
+        for (long k = 1;; ++k) {
+            const long ti = std::max(1L, k * slots / tiles_c);
+            const long cpb = (((long)n + ti - 1) / ti + unit - 1) / unit * unit;
+            if (cpb <= 160 || ti >= n)
+                return (int)cpb;
+        }
+    }
     // When the CUs hold fewer than 3.5 workgroups each, fill the slots once;
     // else aim at about 2.75 per CU (G900: 20 clients per workgroup measured
     // 2 % faster than 16, 12 and 32 slower)
