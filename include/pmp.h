@@ -89,8 +89,9 @@ typedef struct pmp_ga pmp_ga;
  * Errors: PMP_EINVAL for sizes (m above PMP_MAX_EVAL_FACILITIES included),
  * null pointers, PMP_ASYNC without PMP_ON_DEVICE, or any d_ij < 0 (the paper
  * assumes non-negative distances).
- * Rows wider than PMP_MAX_FACILITIES are sorted in device memory (a scratch
- * of up to 256 MB of keys, freed before returning).
+ * Rows of more than 23552 distances are sorted in device memory (a scratch
+ * of up to 256 MB of keys, given back before returning); narrower ones in a
+ * workgroup's LDS.
  * Waits for its stream before returning, except with PMP_ASYNC: the tables
  * are then made on `stream` after the call returns (d must stay valid until
  * they are), negative distances are recorded in the instance's error word
@@ -386,8 +387,8 @@ PMP_API pmp_status pmp_ga_autotune(pmp_ga *ga, int32_t *clients, int32_t *waves,
  *                   population (made again by the first step, identically),
  *                   so every run must be before its first generation
  *                   (PMP_EINVAL otherwise, when the choice is timed).
- *                   Choices are cached per process by the runs' shapes.  Results of the runs do not depend on
- *                   the tiling.  Synchronous on `stream`.  PMP_BATCH_CLIENTS
+ *                   Choices are cached per process by the runs'
+ *                   shapes.  Results of the runs do not depend on the tiling.  Synchronous on `stream`.  PMP_BATCH_CLIENTS
  *                   sets the common count without timing (also at
  *                   pmp_batch_create).
  * pmp_batch_check   wait for `stream`; PMP_EDEVICE if a grid barrier timed

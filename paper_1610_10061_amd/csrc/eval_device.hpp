@@ -26,7 +26,7 @@
 // entries.  This replaces the paper's one-thread-per-chromosome loop: lanes
 // never diverge and Pi' rows are read once per 64 chromosomes.
 //
-// Partial sums of the four waves are combined in LDS and stored, one int64
+// Partial sums of the waves are combined in LDS and stored, one int64
 // per (client tile, chromosome), with plain stores; the consumer (the
 // reduction below or the GA's next stage) adds the client tiles up.  Integer
 // addition makes the result exact and independent of tiling.  Workgroups

@@ -147,8 +147,8 @@ hipError_t launch_nv(const EvalArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t
     return hipGetLastError();
 }
 
-// Waves per workgroup: 4 (the default), 8 or 16; the reduced walk runs
-// with 4.
+// Waves per workgroup: 16 (what the runtime takes unless tuned), 8 or 4; the
+// reduced walk runs with 4.
 template <int WD, bool R, bool H>
 hipError_t launch_wd(const EvalArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
 {

@@ -233,15 +233,6 @@ int paired_scans(int m, int p)
     return (int64_t)m + 1 <= 4LL * ((int64_t)p + 1) ? 1 : 0;
 }
 
-// Clients per workgroup of the evaluation kernel.  A workgroup first stages
-// its chromosome tile (W words per chromosome loaded and turned
-// facility-major), then walks its clients.  With long scans (mean
-// (m+1)/(p+1) of 128 entries or more) the walks dominate: whole rounds of the
-// resident slots, of few enough clients that uneven scan lengths even out.
-// With short scans the staging counts: the fewest
-// client tiles that still give every CU of the device about 2.75
-// workgroups, or that fill every CU's resident slots once when it holds
-// fewer than 3.5, so that no workgroup waits for a slot.
 // Waves per workgroup of the evaluation kernel (4, 8 or 16 waves share one
 // staged chromosome tile).  PMP_EVAL_WAVES forces it.
 int eval_waves(int n, int P, int m, int p, int W)
@@ -303,6 +294,15 @@ int fused_clients_per_block(int n, int P)
     return (int)std::min<long>(f, n);
 }
 
+// Clients per workgroup of the evaluation kernel.  A workgroup first stages
+// its chromosome tile (W words per chromosome loaded and turned
+// facility-major), then walks its clients.  With long scans (mean
+// (m+1)/(p+1) of 128 entries or more) the walks dominate: whole rounds of the
+// resident slots, of few enough clients that uneven scan lengths even out.
+// With short scans the staging counts: the fewest client tiles that still
+// give every CU of the device about 2.75 workgroups, or that fill every CU's
+// resident slots once when it holds fewer than 3.5, so that no workgroup waits
+// for a slot.
 int clients_per_block(int n, int P, int m, int p, int W, bool reduced = false,
                       int waves = kEvalWaves)
 {
