@@ -5,8 +5,13 @@
 // the pages) against 0.2 ms of kernels.  A freed block waits in a cache for
 // the next object that asks for about its size.
 //
-//  - A block enters the cache only when its device has finished all work (the
-//    wait hipFree makes too), so any stream and thread may take it next.
+//  - A block enters the cache only when nothing that uses it is left on the
+//    device, which its object's StreamUse says without asking the device: the
+//    library has waited for everything it enqueued for the object.  Any stream
+//    and thread may take it next.  The blocks of an object whose work may
+//    still run go to hipFree, which waits.  (A wait for the whole device here
+//    instead would not be allowed while any stream of the process is being
+//    captured, by whatever thread, and would spoil that capture.)
 //  - The cache holds at most PMP_DEVICE_CACHE_MB (default 1024) per device;
 //    past that the block freed longest ago goes back to the driver, as does
 //    every block that nobody has asked for in kMaxIdle.  When the driver is
@@ -27,6 +32,104 @@
 
 namespace pmp {
 
+// What the library has enqueued for an object and not waited for: nothing, work
+// on one stream, or work that a wait for one stream does not cover (several
+// streams, a captured graph, the per-thread default stream).  Streams are told
+// apart by their handles.
+class StreamUse {
+public:
+    // Work was enqueued on s, or recorded into a graph that s is captured into
+    // and that may be launched on any stream at any time.
+    void enqueued(hipStream_t s, bool captured)
+    {
+        std::lock_guard<std::mutex> lock(mu_);
+        ++marks_;
+        if (captured || s == hipStreamPerThread || (state_ != kIdle && stream_ != s))
+            state_ = kMany;
+        else if (state_ == kIdle)
+            state_ = kOne;
+        stream_ = s;
+    }
+    // Taken before a wait; waited(s, it) afterwards clears the work on s unless
+    // more was enqueued meanwhile (an instance is used by several runs' calls).
+    uint64_t marks() const
+    {
+        std::lock_guard<std::mutex> lock(mu_);
+        return marks_;
+    }
+    void waited(hipStream_t s, uint64_t marks)
+    {
+        std::lock_guard<std::mutex> lock(mu_);
+        if (state_ == kOne && stream_ == s && marks_ == marks)
+            state_ = kIdle;
+    }
+    bool idle() const
+    {
+        std::lock_guard<std::mutex> lock(mu_);
+        return state_ == kIdle;
+    }
+
+private:
+    enum State { kIdle, kOne, kMany };
+    mutable std::mutex mu_;
+    State state_ = kIdle;
+    hipStream_t stream_ = nullptr;
+    uint64_t marks_ = 0;
+};
+
+// Whether s is being captured into a graph.
+inline bool stream_captured(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();  // (the legacy stream beside a capture)
+        return true;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
+// One entry point's use of its objects on its stream: unless it says that it
+// has waited for the stream, what it enqueued counts as left when it returns.
+class StreamCall {
+public:
+    // (null pointers are skipped)
+    explicit StreamCall(hipStream_t s, StreamUse *a, StreamUse *b = nullptr,
+                        StreamUse *c = nullptr)
+        : s_(s), captured_(stream_captured(s)),
+          uses_{{a, a ? a->marks() : 0}, {b, b ? b->marks() : 0}, {c, c ? c->marks() : 0}}
+    {
+    }
+    void waited()
+    {
+        left_ = false;
+        for (const Use &u : uses_)
+            if (u.use)
+                u.use->waited(s_, u.marks);
+    }
+    // (work enqueued after a wait within the call)
+    void more() { left_ = true; }
+    ~StreamCall()
+    {
+        if (!left_)
+            return;
+        for (const Use &u : uses_)
+            if (u.use)
+                u.use->enqueued(s_, captured_);
+    }
+    StreamCall(const StreamCall &) = delete;
+    StreamCall &operator=(const StreamCall &) = delete;
+
+private:
+    struct Use {
+        StreamUse *use;
+        uint64_t marks;
+    };
+    const hipStream_t s_;
+    const bool captured_;
+    bool left_ = true;
+    const Use uses_[3];
+};
+
 class DevicePool {
 public:
     static DevicePool &get()
@@ -38,29 +141,21 @@ public:
     // Within a CallScope of a stream under capture, blocks come from and go to
     // the driver directly.
     struct CallScope {
-        explicit CallScope(hipStream_t s) : before(direct())
-        {
-            hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-            if (hipStreamIsCapturing(s, &st) != hipSuccess) {
-                (void)hipGetLastError();  // (the legacy stream beside a capture)
-                st = hipStreamCaptureStatusActive;
-            }
-            direct() = st != hipStreamCaptureStatusNone;
-        }
+        explicit CallScope(hipStream_t s) : before(direct()) { direct() = stream_captured(s); }
         ~CallScope() { direct() = before; }
         CallScope(const CallScope &) = delete;
         CallScope &operator=(const CallScope &) = delete;
         const bool before;
     };
 
-    // Several frees with one wait for the device: the scope's first free
-    // waits, the others belong to the same object.
+    // Within a FreeScope(true) freed blocks have no work left on the device
+    // and are kept; elsewhere they go to the driver.
     struct FreeScope {
-        FreeScope() : before(waited()) { waited() = -1; }
-        ~FreeScope() { waited() = before; }
+        explicit FreeScope(bool idle) : before(keep()) { keep() = idle; }
+        ~FreeScope() { keep() = before; }
         FreeScope(const FreeScope &) = delete;
         FreeScope &operator=(const FreeScope &) = delete;
-        const int before;
+        const bool before;
     };
 
     hipError_t alloc(void **out, size_t bytes)
@@ -113,7 +208,7 @@ public:
                 live_.erase(it);
             }
         }
-        if (b.bytes == 0 || b.bytes > limit_ || direct() || !wait_for(b.dev)) {
+        if (b.bytes == 0 || b.bytes > limit_ || direct() || !keep()) {
             (void)hipFree(p);
             return;
         }
@@ -161,30 +256,10 @@ private:
         static thread_local bool d = false;
         return d;
     }
-    // -2: outside a FreeScope; -1: in one, no wait yet; else the device the
-    // scope has waited for
-    static int &waited()
+    static bool &keep()
     {
-        static thread_local int w = -2;
-        return w;
-    }
-
-    // All work of device dev done (false: the wait is not possible now)
-    static bool wait_for(int dev)
-    {
-        if (waited() == dev)
-            return true;
-        int cur = dev;
-        if (hipGetDevice(&cur) != hipSuccess || (cur != dev && hipSetDevice(dev) != hipSuccess))
-            return false;
-        const bool ok = hipDeviceSynchronize() == hipSuccess;
-        if (!ok)
-            (void)hipGetLastError();
-        if (cur != dev)
-            (void)hipSetDevice(cur);
-        if (ok && waited() == -1)
-            waited() = dev;
-        return ok;
+        static thread_local bool k = false;
+        return k;
     }
 
     // Every cached block of a device to the driver; false if there was none.

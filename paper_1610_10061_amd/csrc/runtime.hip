@@ -430,6 +430,7 @@ struct pmp_instance {
     unsigned long long *dtotal = nullptr;  // the sum on the device
     uint32_t *row_err = nullptr;           // n flags of the sort: negative distances
     Arena arena;                           // pi, ds, delta, err, colsum, nearc, dtotal, row_err
+    mutable StreamUse use;                 // calls of this handle, its runs' and its polynomials'
 
     // the sum of d, read back on its first use after an asynchronous
     // preprocessing (which may still be running on its stream)
@@ -495,6 +496,7 @@ struct BatchHost {
     std::vector<int2> place;
     int2 *d_place = nullptr;
     size_t place_cap = 0;
+    StreamUse use;
 
     void drop_graphs()
     {
@@ -503,9 +505,9 @@ struct BatchHost {
         graphs.clear();
     }
 
-    void release()
+    void release(bool idle)
     {
-        DevicePool::FreeScope frees;
+        const DevicePool::FreeScope frees(idle);
         drop_graphs();
         dfree(d_items);
         dfree(d_prefix);
@@ -529,6 +531,7 @@ struct pmp_model {
     uint16_t *xb = nullptr;      // BF16 inputs (rows x 32)
     float *tf = nullptr, *wf = nullptr, *yf = nullptr;  // rows each
     int64_t cap = 0;             // rows the staging holds
+    StreamUse use;               // calls of this handle and of the runs it proposes for
 };
 
 namespace {
@@ -617,6 +620,13 @@ struct pmp_ga {
     int32_t *c12 = nullptr;
     int32_t *near_off = nullptr;
     uint2 *near_q = nullptr;
+    StreamUse use;
+
+    // one call's use of the run, its instance and its model
+    StreamCall call(hipStream_t s)
+    {
+        return StreamCall(s, &use, &inst->use, model ? &model->use : nullptr);
+    }
 
     int64_t ring_rows() const { return (int64_t)LH * LL * prm.population; }
 
@@ -1102,7 +1112,7 @@ void pmp_instance_destroy(pmp_instance *inst)
 {
     if (!inst)
         return;
-    DevicePool::FreeScope frees;
+    const DevicePool::FreeScope frees(inst->use.idle());
     inst->arena.release();
     host_words().give(inst->host_err);
     dfree(inst->h_masks);
@@ -1164,6 +1174,8 @@ pmp_status pmp_preprocess(const int32_t *d, int64_t ld, int32_t n, int32_t m,
         pmp_instance_destroy(inst);
         return fail(PMP_ENOMEM, "device allocation of tables (%zu cells)", cells);
     }
+    const uint64_t marks = inst->use.marks() + 1;
+    inst->use.enqueued(s, stream_captured(s));  // (until the wait below)
     inst->err_now = inst->err + 32;  // (a cache line of its own)
     inst->host_err = host_words().take();
     if (!inst->host_err) {
@@ -1231,11 +1243,13 @@ pmp_status pmp_preprocess(const int32_t *d, int64_t ld, int32_t n, int32_t m,
             st = fail(PMP_EDEVICE, "preprocess: %s", hipGetErrorString(e));
             break;
         }
+        inst->use.waited(s, marks);
         unsigned long long total = 0;
         memcpy(&total, inst->host_err + 2, sizeof total);
         inst->total = (int64_t)total;
         st = status_from_err(*inst->host_err);
     } while (0);
+    const DevicePool::FreeScope frees(inst->use.idle());
     dfree(dd);
     dfree(wide);
     if (st != PMP_OK) {
@@ -1269,14 +1283,17 @@ pmp_status pmp_instance_tables(const pmp_instance *inst, uint16_t *pi,
     const hipMemcpyKind kind = (flags & PMP_ON_DEVICE) ? hipMemcpyDeviceToDevice
                                                         : hipMemcpyDeviceToHost;
     const size_t K = inst->K, pitch = inst->pitch, n = inst->n;
+    StreamCall call(s, &inst->use);
     if (pi)
         HIP_TRY(hipMemcpy2DAsync(pi, K * 2, inst->pi, pitch * 2, K * 2, n, kind, s));
     if (delta)
         HIP_TRY(hipMemcpy2DAsync(delta, K * 4, inst->delta, pitch * 4, K * 4, n, kind, s));
     if (dsorted)
         HIP_TRY(hipMemcpy2DAsync(dsorted, K * 4, inst->ds, pitch * 4, K * 4, n, kind, s));
-    if (!(flags & PMP_ON_DEVICE) || !(flags & PMP_ASYNC))
+    if (!(flags & PMP_ON_DEVICE) || !(flags & PMP_ASYNC)) {
         HIP_TRY(hipStreamSynchronize(s));
+        call.waited();
+    }
     return PMP_OK;
 }
 
@@ -1297,9 +1314,10 @@ struct pmp_hbp {
     uint64_t *h_masks = nullptr;
     size_t part_cap = 0;
     int32_t h_cap = 0;
+    mutable StreamUse use;
     ~pmp_hbp()
     {
-        DevicePool::FreeScope frees;
+        const DevicePool::FreeScope frees(use.idle());
         dfree(rpi);
         dfree(re);
         dfree(rlen);
@@ -1318,9 +1336,10 @@ struct pmp_hbp {
 // Temporaries of one construction, freed on every return.
 struct HbpScratch {
     HbpArgs h{};
+    bool idle = false;  // everything that uses it has been waited for
     ~HbpScratch()
     {
-        DevicePool::FreeScope frees;
+        const DevicePool::FreeScope frees(idle);
         dfree(h.key);
         dfree(h.slot_of);
         dfree(h.posinv);
@@ -1352,6 +1371,7 @@ pmp_status pmp_hbp_reduce(pmp_instance *inst, void *stream, pmp_hbp **out)
     hipStream_t s = (hipStream_t)stream;
     const int n = inst->n, m = inst->m;
     const size_t cells = (size_t)n * inst->pitch;
+    StreamCall call(s, &inst->use);
     HbpScratch sc;
     HbpArgs &h = sc.h;
     h.t = inst->tables();
@@ -1381,6 +1401,8 @@ pmp_status pmp_hbp_reduce(pmp_instance *inst, void *stream, pmp_hbp **out)
     pmp_hbp *r = new pmp_hbp;
     std::unique_ptr<pmp_hbp> guard(r);
     r->inst = inst;
+    r->use.enqueued(s, stream_captured(s));  // (until the last wait below)
+    const uint64_t marks = r->use.marks();
     if (dalloc(&r->rlen_full, (size_t)n))
         return fail(PMP_ENOMEM, "reduced polynomial rows");
     h.rlen_full = r->rlen_full;
@@ -1433,6 +1455,9 @@ pmp_status pmp_hbp_reduce(pmp_instance *inst, void *stream, pmp_hbp **out)
     h.term_coef = r->term_coef;
     HIP_TRY(launch_hbp_emit(h, s));
     HIP_TRY(hipStreamSynchronize(s));
+    call.waited();
+    r->use.waited(s, marks);
+    sc.idle = true;
     *out = guard.release();
     return PMP_OK;
 }
@@ -1462,6 +1487,7 @@ pmp_status pmp_hbp_terms(const pmp_hbp *hp, int32_t *row, int32_t *degree, int64
     const hipMemcpyKind kind =
         (flags & PMP_ON_DEVICE) ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
     const size_t T = (size_t)hp->terms;
+    StreamCall call(s, &hp->use);
     if (row && T)
         HIP_TRY(hipMemcpyAsync(row, hp->term_row, sizeof(int32_t) * T, kind, s));
     if (degree && T)
@@ -1471,6 +1497,7 @@ pmp_status pmp_hbp_terms(const pmp_hbp *hp, int32_t *row, int32_t *degree, int64
     if (row_len)
         HIP_TRY(hipMemcpyAsync(row_len, hp->rlen_full, sizeof(int32_t) * hp->inst->n, kind, s));
     HIP_TRY(hipStreamSynchronize(s));
+    call.waited();
     return PMP_OK;
 }
 
@@ -1488,6 +1515,8 @@ pmp_status pmp_hbp_eval(pmp_hbp *hp, const uint64_t *masks, int32_t P, int64_t *
     pmp_instance *inst = hp->inst;
     hipStream_t s = (hipStream_t)stream;
     const DevicePool::CallScope scope(s);
+    const DevicePool::FreeScope frees(hp->use.idle());  // (regrown buffers)
+    StreamCall call(s, &hp->use, &inst->use);
     const bool on_dev = flags & PMP_ON_DEVICE;
     const bool async = on_dev && (flags & PMP_ASYNC);
     const size_t W = inst->W;
@@ -1549,6 +1578,7 @@ pmp_status pmp_hbp_eval(pmp_hbp *hp, const uint64_t *masks, int32_t P, int64_t *
     if (async)
         return PMP_OK;
     HIP_TRY(hipStreamSynchronize(s));
+    call.waited();
     return status_from_err(*inst->host_err);
 }
 
@@ -1566,6 +1596,7 @@ struct ApspCache {
         uint32_t *work = nullptr, *wmax = nullptr, *host_wmax = nullptr;
         int32_t *w = nullptr, *d = nullptr;  // staging for host arguments
         size_t work_cap = 0, stage_cap = 0;
+        StreamUse use;
     };
     std::map<int, Dev> dev;
 };
@@ -1593,6 +1624,8 @@ pmp_status pmp_apsp(const int32_t *w, int64_t ldw, int32_t n, int32_t *d, int64_
     std::lock_guard<std::mutex> lock(cache.mu);
     ApspCache::Dev &b = cache.dev[device];
     const size_t cells = (size_t)ld * ld;
+    const DevicePool::FreeScope frees(b.use.idle());  // (regrown buffers)
+    StreamCall call(s, &b.use);
     if (b.work_cap < cells) {
         dfree(b.work);
         b.work_cap = 0;
@@ -1627,6 +1660,7 @@ pmp_status pmp_apsp(const int32_t *w, int64_t ldw, int32_t n, int32_t *d, int64_
     HIP_TRY(launch_apsp_rounds(b.work, n, s));
     HIP_TRY(launch_apsp_out(b.work, n, dd, ldd_dev, b.wmax, b.host_wmax, s));
     HIP_TRY(hipStreamSynchronize(s));
+    call.waited();
     // (an update never exceeds INF, so with weights too large for int32 paths
     // the rounds have only been of no use)
     const uint32_t wmax = *b.host_wmax;
@@ -1635,8 +1669,10 @@ pmp_status pmp_apsp(const int32_t *w, int64_t ldw, int32_t n, int32_t *d, int64_
                     (long long)(n - 1) * (long long)wmax);
     if (on_dev)
         return PMP_OK;
+    call.more();
     HIP_TRY(copy_rows(d, ldd, b.d, n, n, n, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
+    call.waited();
     return PMP_OK;
 }
 
@@ -1646,9 +1682,12 @@ pmp_status pmp_instance_check(pmp_instance *inst, void *stream)
         return fail(PMP_EINVAL, "instance is NULL");
     hipStream_t s = (hipStream_t)stream;
     uint32_t herr = 0;
+    StreamCall call(s, &inst->use);
     HIP_TRY(hipStreamSynchronize(s));
     HIP_TRY(hipMemcpy(&herr, inst->err, sizeof herr, hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemset(inst->err, 0, sizeof herr));
+    HIP_TRY(launch_zero(inst->err, sizeof herr, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    call.waited();
     return status_from_err(herr);
 }
 
@@ -1674,6 +1713,8 @@ pmp_status pmp_eval_population(pmp_instance *inst, const uint64_t *masks,
                     PMP_MAX_FACILITIES);
     hipStream_t s = (hipStream_t)stream;
     const DevicePool::CallScope scope(s);
+    const DevicePool::FreeScope frees(inst->use.idle());  // (regrown buffers)
+    StreamCall call(s, &inst->use);
     const bool on_dev = flags & PMP_ON_DEVICE;
     const bool async = on_dev && (flags & PMP_ASYNC);
     const size_t W = inst->W;
@@ -1770,11 +1811,13 @@ pmp_status pmp_eval_population(pmp_instance *inst, const uint64_t *masks,
         return PMP_OK;
     if (folded) {
         HIP_TRY(hipStreamSynchronize(s));
+        call.waited();
         return status_from_err(*inst->host_err);
     }
     uint32_t herr = 0;
     HIP_TRY(hipMemcpyAsync(&herr, inst->err, sizeof herr, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
+    call.waited();
     return status_from_err(herr);
 }
 
@@ -1804,6 +1847,7 @@ pmp_status pmp_eval_population_noalloc(pmp_instance *inst, const uint64_t *masks
         return fail(PMP_EINVAL, "masks or fitness is NULL");
     hipStream_t s = (hipStream_t)stream;
     const bool async = flags & PMP_ASYNC;
+    StreamCall call(s, &inst->use);
     void *ws = nullptr;
     HIP_TRY(scratch_address(&ws));
 
@@ -1838,6 +1882,7 @@ pmp_status pmp_eval_population_noalloc(pmp_instance *inst, const uint64_t *masks
     if (async)
         return PMP_OK;
     HIP_TRY(hipStreamSynchronize(s));
+    call.waited();
     return status_from_err(*inst->host_err);
 }
 
@@ -1845,7 +1890,8 @@ void pmp_ga_destroy(pmp_ga *ga)
 {
     if (!ga)
         return;
-    DevicePool::FreeScope frees;
+    const bool idle = ga->use.idle();
+    const DevicePool::FreeScope frees(idle);
     ga->arena.release();  // (clears its members: the frees below skip them)
     ga->parts.release();
     for (int k = 0; k < 2; ++k) {
@@ -1871,7 +1917,7 @@ void pmp_ga_destroy(pmp_ga *ga)
     dfree(ga->report);
     ga->free_learned();
     if (ga->self) {
-        ga->self->release();
+        ga->self->release(idle);
         delete ga->self;
     }
     if (ga->gexec)
@@ -1952,6 +1998,8 @@ pmp_status pmp_ga_create(pmp_instance *inst, const pmp_ga_params *prm,
     }
     // every buffer of the arena starts at zero (populations, fitness, bests,
     // counters, barrier and arrival words), then the run state
+    ga->use.enqueued(nullptr, false);  // (until the wait below)
+    const uint64_t marks = ga->use.marks();
     hipError_t e = ga->arena.zero();
     unsigned long long init[GS_COUNT] = {0};
     init[GS_BEST] = (unsigned long long)INT64_MAX;
@@ -1975,6 +2023,7 @@ pmp_status pmp_ga_create(pmp_instance *inst, const pmp_ga_params *prm,
         pmp_ga_destroy(ga);
         return fail(PMP_EDEVICE, "GA state init: %s", hipGetErrorString(e));
     }
+    ga->use.waited(nullptr, marks);
     *out = ga;
     return PMP_OK;
 }
@@ -2267,6 +2316,8 @@ pmp_status pmp_ga_step(pmp_ga *ga, int32_t generations, void *stream)
         return PMP_OK;
     hipStream_t s = (hipStream_t)stream;
     const DevicePool::CallScope scope(s);
+    const DevicePool::FreeScope frees(ga->use.idle());  // (regrown buffers)
+    const StreamCall call = ga->call(s);
     if (!ga->persistent && ga->spec() && ga->ensure_spec() != hipSuccess)
         return fail(PMP_ENOMEM, "mutation-cycle buffers for P=%d, Y=%d", ga->prm.population,
                     ga->Y);
@@ -2312,7 +2363,9 @@ pmp_status pmp_ga_best(pmp_ga *ga, uint64_t *mask, int64_t *cost,
         return fail(PMP_EINVAL, "ga is NULL");
     hipStream_t s = (hipStream_t)stream;
     std::vector<unsigned long long> r;
+    StreamCall call = ga->call(s);
     HIP_TRY(ga_report(ga, s, r));
+    call.waited();
     const unsigned long long *gs = r.data() + RP_GS;
     if (mask)
         for (int w = 0; w < ga->inst->W; ++w)
@@ -2345,7 +2398,9 @@ pmp_status pmp_ga_state(pmp_ga *ga, uint64_t *population, int64_t *fitness,
     if (!ga)
         return fail(PMP_EINVAL, "ga is NULL");
     hipStream_t s = (hipStream_t)stream;
+    StreamCall call = ga->call(s);
     HIP_TRY(hipStreamSynchronize(s));
+    call.waited();  // (the copies below wait by themselves)
     const size_t W = ga->inst->W, P = ga->prm.population, NB = ga->NB;
     const int f = ga->final_buf();
     if (population)
@@ -2368,7 +2423,9 @@ pmp_status pmp_ga_profile(pmp_ga *ga, int32_t enable)
         return fail(PMP_EINVAL, "ga is NULL");
     HIP_TRY(hipDeviceSynchronize());
     unsigned long long tot[CS_COUNT];
+    StreamCall call = ga->call(nullptr);
     HIP_TRY(ga_counters(ga, tot));
+    call.waited();
     ga->prof = enable != 0;
     ga->ev_used = 0;
     ga->base_scan = tot[CS_SCAN] + tot[CS_SPEC_SCAN];
@@ -2382,7 +2439,9 @@ pmp_status pmp_ga_profile_read(pmp_ga *ga, pmp_profile *out, void *stream)
         return fail(PMP_EINVAL, "ga or out is NULL");
     hipStream_t s = (hipStream_t)stream;
     unsigned long long tot[CS_COUNT];
+    StreamCall call = ga->call(s);
     HIP_TRY(ga_counters(ga, tot, s));  // (waits for the stream)
+    call.waited();
     double ms = 0;
     for (size_t k = 0; k + 1 < ga->ev_used; k += 2) {
         float t = 0;
@@ -2409,7 +2468,9 @@ pmp_status pmp_ga_autotune(pmp_ga *ga, int32_t *clients, int32_t *waves, void *s
     if (!ga)
         return fail(PMP_EINVAL, "ga is NULL");
     hipStream_t s = (hipStream_t)stream;
+    StreamCall call = ga->call(s);
     HIP_TRY(hipStreamSynchronize(s));
+    call.waited();
     unsigned long long gs[GS_COUNT];
     HIP_TRY(hipMemcpy(gs, ga->gs, sizeof gs, hipMemcpyDeviceToHost));
     if (gs[GS_GEN] != 0)
@@ -2442,6 +2503,7 @@ pmp_status pmp_ga_autotune(pmp_ga *ga, int32_t *clients, int32_t *waves, void *s
         // mutation cycle is evaluated at once) Y copies of it standing in for
         // the mutants, whose evaluation runs with the same waves
         GaArgs g = ga->args();
+        call.more();
         HIP_TRY(launch_ga_init(g, s));
         const bool spec = ga->spec();
         const size_t PY = (size_t)P * ga->Y, W = inst->W;
@@ -2541,9 +2603,14 @@ pmp_status pmp_ga_autotune(pmp_ga *ga, int32_t *clients, int32_t *waves, void *s
             (void)hipEventDestroy(e0);
         if (e1)
             (void)hipEventDestroy(e1);
-        dfree(part);
-        dfree(spart);
-        dfree(stand_in);
+        if (e == hipSuccess)  // (every trial was waited for)
+            call.waited();
+        {
+            const DevicePool::FreeScope frees(e == hipSuccess);
+            dfree(part);
+            dfree(spart);
+            dfree(stand_in);
+        }
         if (e != hipSuccess)
             return fail(PMP_EDEVICE, "autotune: %s", hipGetErrorString(e));
         std::lock_guard<std::mutex> lock(mu);
@@ -2553,12 +2620,13 @@ pmp_status pmp_ga_autotune(pmp_ga *ga, int32_t *clients, int32_t *waves, void *s
     ga->spec_waves = best_w;
     if (best != ga->cpb) {
         const int ti = (n + best - 1) / best;
+        const DevicePool::FreeScope frees(ga->use.idle());
         if (ga->carve_parts(std::max(ti, ga->fTI)) != hipSuccess)
             return fail(PMP_ENOMEM, "GA partial sums for %d client tiles", ti);
         ga->cpb = best;
         ga->TI = ti;
         if (ga->self) {
-            ga->self->release();
+            ga->self->release(ga->use.idle());
             delete ga->self;
             ga->self = nullptr;
         }
@@ -2593,7 +2661,7 @@ pmp_status pmp_batch_create(pmp_ga *const *gas, int32_t count, pmp_batch **out)
     pmp_batch *bt = new pmp_batch;
     hipError_t e = batch_build(bt->bh, gas, count);
     if (e != hipSuccess) {
-        bt->bh.release();
+        bt->bh.release(false);
         delete bt;
         return fail(PMP_ENOMEM, "batch set-up: %s", hipGetErrorString(e));
     }
@@ -2612,7 +2680,9 @@ pmp_status pmp_batch_autotune(pmp_batch *bt, int32_t *clients, void *stream)
         return fail(PMP_EINVAL, "batch is NULL");
     hipStream_t s = (hipStream_t)stream;
     BatchHost &bh = bt->bh;
+    StreamCall call(s, &bh.use);
     HIP_TRY(hipStreamSynchronize(s));
+    call.waited();
     if (env_int("PMP_BATCH_CLIENTS", 0) > 0) {  // set by hand: no timing
         if (clients)
             *clients = bh.clients;
@@ -2647,8 +2717,11 @@ pmp_status pmp_batch_autotune(pmp_batch *bt, int32_t *clients, void *stream)
         if (gen != 0)
             return fail(PMP_EINVAL, "autotune a batch before its first step (run %zu)", b);
     }
-    for (pmp_ga *ga : bh.gas)
+    call.more();
+    for (pmp_ga *ga : bh.gas) {
+        const StreamCall run = ga->call(s);
         HIP_TRY(launch_ga_init(ga->args(), s));
+    }
     hipEvent_t e0 = nullptr, e1 = nullptr;
     hipError_t e = hipEventCreate(&e0);
     if (e == hipSuccess)
@@ -2700,6 +2773,7 @@ pmp_status pmp_batch_autotune(pmp_batch *bt, int32_t *clients, void *stream)
         e = hipStreamSynchronize(s);
     if (e != hipSuccess)
         return fail(PMP_EDEVICE, "batch autotune: %s", hipGetErrorString(e));
+    call.waited();
     {
         std::lock_guard<std::mutex> lock(mu);
         cache[key] = best;
@@ -2719,6 +2793,19 @@ pmp_status pmp_batch_step(pmp_batch *bt, int32_t generations, void *stream)
         return PMP_OK;
     hipStream_t s = (hipStream_t)stream;
     BatchHost &bh = bt->bh;
+    struct Left {  // (on every way out: this call does not wait)
+        BatchHost &bh;
+        hipStream_t s;
+        bool captured;
+        ~Left()
+        {
+            bh.use.enqueued(s, captured);
+            for (pmp_ga *ga : bh.gas) {
+                ga->use.enqueued(s, captured);
+                ga->inst->use.enqueued(s, captured);
+            }
+        }
+    } left{bh, s, stream_captured(s)};
     for (pmp_ga *ga : bh.gas)  // the batch kernels make each generation's population
         ga->init_ahead = false;
     if (!bt->graphs || bt->prof) {
@@ -2756,7 +2843,9 @@ pmp_status pmp_batch_check(pmp_batch *bt, int32_t *grid, void *stream)
 {
     if (!bt)
         return fail(PMP_EINVAL, "batch is NULL");
+    StreamCall call((hipStream_t)stream, &bt->bh.use);
     HIP_TRY(hipStreamSynchronize((hipStream_t)stream));
+    call.waited();
     uint32_t herr = 0;
     HIP_TRY(hipMemcpy(&herr, bt->bh.d_err, sizeof herr, hipMemcpyDeviceToHost));
     if (grid)
@@ -2768,7 +2857,7 @@ void pmp_batch_destroy(pmp_batch *bt)
 {
     if (!bt)
         return;
-    bt->bh.release();
+    bt->bh.release(bt->bh.use.idle());
     for (hipEvent_t e : bt->ev)
         (void)hipEventDestroy(e);
     delete bt;
@@ -2791,7 +2880,9 @@ pmp_status pmp_batch_profile_read(pmp_batch *bt, double *eval_ms, int64_t *eval_
 {
     if (!bt)
         return fail(PMP_EINVAL, "batch is NULL");
+    StreamCall call((hipStream_t)stream, &bt->bh.use);
     HIP_TRY(hipStreamSynchronize((hipStream_t)stream));
+    call.waited();
     double ms = 0;
     for (int k = 0; k + 1 < bt->ev_used; k += 2) {
         float t = 0;
@@ -2878,6 +2969,7 @@ pmp_status pmp_features(pmp_instance *inst, const uint64_t *masks, int32_t P,
         return fail(PMP_EDEVICE, "sum of d of the instance");
     hipStream_t s = (hipStream_t)stream;
     const DevicePool::CallScope scope(s);
+    StreamCall call(s, &inst->use);
     const bool on_dev = flags & PMP_ON_DEVICE;
     const size_t W = inst->W, cells = (size_t)P * inst->m * kFeatures;
     const uint64_t *dm = masks;
@@ -2885,6 +2977,7 @@ pmp_status pmp_features(pmp_instance *inst, const uint64_t *masks, int32_t P,
     uint64_t *tm = nullptr;
     float *to = nullptr;
     pmp_status st = PMP_OK;
+    bool idle = false;
     do {
         if (!on_dev) {
             if (dalloc(&tm, (size_t)P * W) || dalloc(&to, cells)) {
@@ -2922,8 +3015,11 @@ pmp_status pmp_features(pmp_instance *inst, const uint64_t *masks, int32_t P,
             st = fail(PMP_EDEVICE, "features: %s", hipGetErrorString(e));
             break;
         }
+        call.waited();
+        idle = true;
         st = status_from_err(herr);
     } while (0);
+    const DevicePool::FreeScope frees(idle);
     dfree(tm);
     dfree(to);
     return st;
@@ -2933,7 +3029,7 @@ void pmp_model_destroy(pmp_model *md)
 {
     if (!md)
         return;
-    DevicePool::FreeScope frees;
+    const DevicePool::FreeScope frees(md->use.idle());
     dfree(md->d.master);
     dfree(md->d.m1);
     dfree(md->d.m2);
@@ -2968,6 +3064,8 @@ pmp_status pmp_model_create(uint64_t seed, pmp_model **out)
         pmp_model_destroy(md);
         return fail(PMP_ENOMEM, "model buffers");
     }
+    md->use.enqueued(nullptr, false);  // (until the wait below)
+    const uint64_t marks = md->use.marks();
     hipError_t e = launch_mlp_init(d, seed, nullptr);
     if (e == hipSuccess)
         e = hipDeviceSynchronize();
@@ -2975,6 +3073,7 @@ pmp_status pmp_model_create(uint64_t seed, pmp_model **out)
         pmp_model_destroy(md);
         return fail(PMP_EDEVICE, "model init: %s", hipGetErrorString(e));
     }
+    md->use.waited(nullptr, marks);
     *out = md;
     return PMP_OK;
 }
@@ -2985,10 +3084,13 @@ pmp_status pmp_model_get(pmp_model *md, float *params, uint32_t flags, void *str
         return fail(PMP_EINVAL, "model or params is NULL");
     hipStream_t s = (hipStream_t)stream;
     const bool on_dev = flags & PMP_ON_DEVICE;
+    StreamCall call(s, &md->use);
     HIP_TRY(hipMemcpyAsync(params, md->d.master, sizeof(float) * kParams,
                            on_dev ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s));
-    if (!on_dev)
+    if (!on_dev) {
         HIP_TRY(hipStreamSynchronize(s));
+        call.waited();
+    }
     return PMP_OK;
 }
 
@@ -2998,14 +3100,17 @@ pmp_status pmp_model_set(pmp_model *md, const float *params, uint32_t flags, voi
         return fail(PMP_EINVAL, "model or params is NULL");
     hipStream_t s = (hipStream_t)stream;
     const bool on_dev = flags & PMP_ON_DEVICE;
+    StreamCall call(s, &md->use);
     HIP_TRY(hipMemcpyAsync(md->d.master, params, sizeof(float) * kParams,
                            on_dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s));
     HIP_TRY(launch_zero(md->d.m1, sizeof(float) * kParams, s));
     HIP_TRY(launch_zero(md->d.m2, sizeof(float) * kParams, s));
     HIP_TRY(launch_zero(md->d.step, sizeof(uint32_t), s));
     HIP_TRY(launch_mlp_publish(md->d, s));
-    if (!on_dev)
+    if (!on_dev) {
         HIP_TRY(hipStreamSynchronize(s));
+        call.waited();
+    }
     return PMP_OK;
 }
 
@@ -3017,6 +3122,7 @@ pmp_status model_stage(pmp_model *md, const float *x, const float *t, const floa
                        const float **dw)
 {
     const DevicePool::CallScope scope(s);
+    const DevicePool::FreeScope frees(md->use.idle());  // (regrown buffers)
     if (md->cap < rows) {
         dfree(md->xf);
         dfree(md->xb);
@@ -3068,6 +3174,7 @@ pmp_status pmp_model_forward(pmp_model *md, const float *x, int32_t rows, float 
         return fail(PMP_EINVAL, "x or y is NULL");
     hipStream_t s = (hipStream_t)stream;
     const bool on_dev = flags & PMP_ON_DEVICE;
+    StreamCall call(s, &md->use);
     pmp_status st = model_stage(md, x, nullptr, nullptr, rows, on_dev, s, nullptr, nullptr);
     if (st != PMP_OK)
         return st;
@@ -3076,6 +3183,7 @@ pmp_status pmp_model_forward(pmp_model *md, const float *x, int32_t rows, float 
     if (!on_dev) {
         HIP_TRY(hipMemcpyAsync(y, dy, sizeof(float) * rows, hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
+        call.waited();
     }
     return PMP_OK;
 }
@@ -3092,6 +3200,7 @@ pmp_status model_steps(pmp_model *md, const float *x, const float *t, const floa
         return fail(PMP_EINVAL, "need rows >= 1, x and t");
     const bool on_dev = flags & PMP_ON_DEVICE;
     const float *dt = nullptr, *dw = nullptr;
+    StreamCall call(s, &md->use);
     pmp_status st = model_stage(md, x, t, w, rows, on_dev, s, &dt, &dw);
     if (st != PMP_OK)
         return st;
@@ -3114,8 +3223,10 @@ pmp_status model_steps(pmp_model *md, const float *x, const float *t, const floa
     if (loss)
         HIP_TRY(hipMemcpyAsync(loss, md->loss, sizeof(float),
                                on_dev ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s));
-    if (!on_dev)
+    if (!on_dev) {
         HIP_TRY(hipStreamSynchronize(s));
+        call.waited();
+    }
     return PMP_OK;
 }
 
@@ -3147,6 +3258,7 @@ pmp_status pmp_ga_set_model(pmp_ga *ga, pmp_model *model, const pmp_learn_params
         ga->gexec = nullptr;
     }
     if (!model) {
+        const DevicePool::FreeScope frees(ga->use.idle());
         ga->model = nullptr;
         ga->free_learned();
         return PMP_OK;
@@ -3180,8 +3292,12 @@ pmp_status pmp_ga_set_model(pmp_ga *ga, pmp_model *model, const pmp_learn_params
     const float lr = q.lr == 0.f ? 1e-3f : q.lr;
     if (!(lr > 0.f) || lr > 1.f)
         return fail(PMP_EINVAL, "lr outside (0, 1]");
-    ga->free_learned();
+    {
+        const DevicePool::FreeScope frees(ga->use.idle());
+        ga->free_learned();
+    }
     ga->model = nullptr;
+    StreamCall call(nullptr, &ga->use, &ga->inst->use);
     const size_t P = ga->prm.population, R = (size_t)H * L * P;
     if (dalloc(&ga->swaps, P * L * 2) || dalloc(&ga->rep_x, R * kIn) || dalloc(&ga->rep_t, R) ||
         dalloc(&ga->rep_w, R) || dalloc(&ga->rep_jk, R * 2) || dalloc(&ga->rep_d, R * 2) ||
@@ -3212,6 +3328,7 @@ pmp_status pmp_ga_set_model(pmp_ga *ga, pmp_model *model, const pmp_learn_params
         ga->free_learned();
         return fail(PMP_EDEVICE, "learned proposal init: %s", hipGetErrorString(e));
     }
+    call.waited();
     ga->walk_shape = env_int("PMP_WALK", 0);
     if (ga->walk_shape == 0) {
         // the two-pass walk's buffers and the facility index of the rows'
@@ -3229,6 +3346,7 @@ pmp_status pmp_ga_set_model(pmp_ga *ga, pmp_model *model, const pmp_learn_params
             ga->free_learned();
             return fail(PMP_ENOMEM, "two-pass walk buffers (%zu pairs)", PN);
         }
+        call.more();
         e = hipMemset(cursor, 0, sizeof(int32_t) * t.m);
         if (e == hipSuccess)
             e = launch_near_count(t, cursor, nullptr);
@@ -3245,11 +3363,15 @@ pmp_status pmp_ga_set_model(pmp_ga *ga, pmp_model *model, const pmp_learn_params
             e = launch_near_fill(t, cursor, ga->near_q, nullptr);
         if (e == hipSuccess)
             e = hipDeviceSynchronize();
-        dfree(cursor);
+        {
+            const DevicePool::FreeScope frees(e == hipSuccess);
+            dfree(cursor);
+        }
         if (e != hipSuccess) {
             ga->free_learned();
             return fail(PMP_EDEVICE, "facility index: %s", hipGetErrorString(e));
         }
+        call.waited();
     }
     ga->model = model;
     ga->LC = C;
@@ -3269,7 +3391,9 @@ pmp_status pmp_ga_replay(pmp_ga *ga, int32_t *rows, uint16_t *x, float *target,
         return fail(PMP_EINVAL, "ga is NULL");
     if (!ga->model)
         return fail(PMP_EINVAL, "the run has no model");
+    StreamCall call = ga->call((hipStream_t)stream);
     HIP_TRY(hipStreamSynchronize((hipStream_t)stream));
+    call.waited();
     const size_t R = (size_t)ga->ring_rows();
     if (rows)
         *rows = (int32_t)R;
@@ -3323,6 +3447,8 @@ pmp_status pmp_exhaustive(pmp_instance *inst, uint64_t *best_mask, int64_t *best
     unsigned long long *part = nullptr;
     int *bi = nullptr;
     pmp_status st = PMP_OK;
+    StreamCall call(s, &inst->use);
+    bool idle = false;
     do {
         if (dalloc(&d_binom, binom.size()) || dalloc(&fit, (size_t)B) || dalloc(&bc, (size_t)nblk) ||
             dalloc(&bi, (size_t)nblk) || dalloc(&run, 2) || dalloc(&masks, (size_t)B * W) ||
@@ -3367,6 +3493,8 @@ pmp_status pmp_exhaustive(pmp_instance *inst, uint64_t *best_mask, int64_t *best
             st = fail(PMP_EDEVICE, "enumeration: %s", hipGetErrorString(e));
             break;
         }
+        call.waited();
+        idle = true;
         st = status_from_err(herr);
         if (st != PMP_OK)
             break;
@@ -3391,6 +3519,7 @@ pmp_status pmp_exhaustive(pmp_instance *inst, uint64_t *best_mask, int64_t *best
             }
         }
     } while (0);
+    const DevicePool::FreeScope frees(idle);
     dfree(d_binom);
     dfree(fit);
     dfree(bc);
