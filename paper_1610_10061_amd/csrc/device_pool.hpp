@@ -17,8 +17,9 @@
 //    every block that nobody has asked for in kMaxIdle.  When the driver is
 //    out of memory everything cached goes back and the allocation is tried
 //    again.
-//  - While the calling entry point's stream is being captured the cache is
-//    left alone: the driver is asked, as without one, and decides.
+//  - While the stream of the calling entry point is being captured (every
+//    entry point that takes a stream opens a CallScope) the cache is left
+//    alone: the driver is asked, as without one, and decides.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -77,25 +78,46 @@ private:
     uint64_t marks_ = 0;
 };
 
-// Whether s is being captured into a graph.
-inline bool stream_captured(hipStream_t s)
-{
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
-        (void)hipGetLastError();  // (the legacy stream beside a capture)
-        return true;
+// An entry point's stream: within the scope of one that is being captured into
+// a graph, blocks come from and go to the driver directly.
+class CallScope {
+public:
+    explicit CallScope(hipStream_t s) : captured(stream_captured(s)), before_(direct())
+    {
+        direct() = captured;
     }
-    return st != hipStreamCaptureStatusNone;
-}
+    ~CallScope() { direct() = before_; }
+    CallScope(const CallScope &) = delete;
+    CallScope &operator=(const CallScope &) = delete;
+    const bool captured;
+
+    static bool &direct()
+    {
+        static thread_local bool d = false;
+        return d;
+    }
+
+private:
+    static bool stream_captured(hipStream_t s)
+    {
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+            (void)hipGetLastError();  // (the legacy stream beside a capture)
+            return true;
+        }
+        return st != hipStreamCaptureStatusNone;
+    }
+    const bool before_;
+};
 
 // One entry point's use of its objects on its stream: unless it says that it
 // has waited for the stream, what it enqueued counts as left when it returns.
-class StreamCall {
+class StreamCall : public CallScope {
 public:
     // (null pointers are skipped)
     explicit StreamCall(hipStream_t s, StreamUse *a, StreamUse *b = nullptr,
                         StreamUse *c = nullptr)
-        : s_(s), captured_(stream_captured(s)),
+        : CallScope(s), s_(s),
           uses_{{a, a ? a->marks() : 0}, {b, b ? b->marks() : 0}, {c, c ? c->marks() : 0}}
     {
     }
@@ -114,10 +136,8 @@ public:
             return;
         for (const Use &u : uses_)
             if (u.use)
-                u.use->enqueued(s_, captured_);
+                u.use->enqueued(s_, captured);
     }
-    StreamCall(const StreamCall &) = delete;
-    StreamCall &operator=(const StreamCall &) = delete;
 
 private:
     struct Use {
@@ -125,7 +145,6 @@ private:
         uint64_t marks;
     };
     const hipStream_t s_;
-    const bool captured_;
     bool left_ = true;
     const Use uses_[3];
 };
@@ -137,16 +156,6 @@ public:
         static DevicePool *p = new DevicePool;  // never destroyed: outlives the runtime
         return *p;
     }
-
-    // Within a CallScope of a stream under capture, blocks come from and go to
-    // the driver directly.
-    struct CallScope {
-        explicit CallScope(hipStream_t s) : before(direct()) { direct() = stream_captured(s); }
-        ~CallScope() { direct() = before; }
-        CallScope(const CallScope &) = delete;
-        CallScope &operator=(const CallScope &) = delete;
-        const bool before;
-    };
 
     // Within a FreeScope(true) freed blocks have no work left on the device
     // and are kept; elsewhere they go to the driver.
@@ -166,7 +175,7 @@ public:
         hipError_t e = hipGetDevice(&dev);
         if (e != hipSuccess)
             return e;
-        if (!direct()) {
+        if (!CallScope::direct()) {
             std::lock_guard<std::mutex> lock(mu_);
             auto best = cached_.end();
             for (auto it = cached_.begin(); it != cached_.end(); ++it)
@@ -182,7 +191,7 @@ public:
             }
         }
         e = hipMalloc(out, bytes);
-        if (e == hipErrorOutOfMemory && !direct() && give_back(dev)) {
+        if (e == hipErrorOutOfMemory && !CallScope::direct() && give_back(dev)) {
             (void)hipGetLastError();
             e = hipMalloc(out, bytes);
         }
@@ -208,7 +217,7 @@ public:
                 live_.erase(it);
             }
         }
-        if (b.bytes == 0 || b.bytes > limit_ || direct() || !keep()) {
+        if (b.bytes == 0 || b.bytes > limit_ || CallScope::direct() || !keep()) {
             (void)hipFree(p);
             return;
         }
@@ -251,11 +260,6 @@ private:
         limit_ = (size_t)(v && *v ? std::max(0L, std::atol(v)) : 1024L) << 20;
     }
 
-    static bool &direct()
-    {
-        static thread_local bool d = false;
-        return d;
-    }
     static bool &keep()
     {
         static thread_local bool k = false;

@@ -1153,6 +1153,7 @@ pmp_status pmp_preprocess(const int32_t *d, int64_t ld, int32_t n, int32_t m,
                     return fail(PMP_EINVAL, "d[%lld][%lld] < 0", (long long)i,
                                 (long long)j);
     }
+    const CallScope scope(s);
     pmp_instance *inst = new pmp_instance;
     inst->n = n;
     inst->m = m;
@@ -1175,7 +1176,7 @@ pmp_status pmp_preprocess(const int32_t *d, int64_t ld, int32_t n, int32_t m,
         return fail(PMP_ENOMEM, "device allocation of tables (%zu cells)", cells);
     }
     const uint64_t marks = inst->use.marks() + 1;
-    inst->use.enqueued(s, stream_captured(s));  // (until the wait below)
+    inst->use.enqueued(s, scope.captured);  // (until the wait below)
     inst->err_now = inst->err + 32;  // (a cache line of its own)
     inst->host_err = host_words().take();
     if (!inst->host_err) {
@@ -1401,7 +1402,7 @@ pmp_status pmp_hbp_reduce(pmp_instance *inst, void *stream, pmp_hbp **out)
     pmp_hbp *r = new pmp_hbp;
     std::unique_ptr<pmp_hbp> guard(r);
     r->inst = inst;
-    r->use.enqueued(s, stream_captured(s));  // (until the last wait below)
+    r->use.enqueued(s, call.captured);  // (until the last wait below)
     const uint64_t marks = r->use.marks();
     if (dalloc(&r->rlen_full, (size_t)n))
         return fail(PMP_ENOMEM, "reduced polynomial rows");
@@ -1514,7 +1515,6 @@ pmp_status pmp_hbp_eval(pmp_hbp *hp, const uint64_t *masks, int32_t P, int64_t *
         return fail(PMP_EINVAL, "masks or fitness is NULL");
     pmp_instance *inst = hp->inst;
     hipStream_t s = (hipStream_t)stream;
-    const DevicePool::CallScope scope(s);
     const DevicePool::FreeScope frees(hp->use.idle());  // (regrown buffers)
     StreamCall call(s, &hp->use, &inst->use);
     const bool on_dev = flags & PMP_ON_DEVICE;
@@ -1712,7 +1712,6 @@ pmp_status pmp_eval_population(pmp_instance *inst, const uint64_t *masks,
         return fail(PMP_EUNSUPPORTED, "the per-chromosome and per-client schemes take m <= %d",
                     PMP_MAX_FACILITIES);
     hipStream_t s = (hipStream_t)stream;
-    const DevicePool::CallScope scope(s);
     const DevicePool::FreeScope frees(inst->use.idle());  // (regrown buffers)
     StreamCall call(s, &inst->use);
     const bool on_dev = flags & PMP_ON_DEVICE;
@@ -2315,7 +2314,6 @@ pmp_status pmp_ga_step(pmp_ga *ga, int32_t generations, void *stream)
     if (generations == 0)
         return PMP_OK;
     hipStream_t s = (hipStream_t)stream;
-    const DevicePool::CallScope scope(s);
     const DevicePool::FreeScope frees(ga->use.idle());  // (regrown buffers)
     const StreamCall call = ga->call(s);
     if (!ga->persistent && ga->spec() && ga->ensure_spec() != hipSuccess)
@@ -2793,6 +2791,7 @@ pmp_status pmp_batch_step(pmp_batch *bt, int32_t generations, void *stream)
         return PMP_OK;
     hipStream_t s = (hipStream_t)stream;
     BatchHost &bh = bt->bh;
+    const CallScope scope(s);
     struct Left {  // (on every way out: this call does not wait)
         BatchHost &bh;
         hipStream_t s;
@@ -2805,7 +2804,7 @@ pmp_status pmp_batch_step(pmp_batch *bt, int32_t generations, void *stream)
                 ga->inst->use.enqueued(s, captured);
             }
         }
-    } left{bh, s, stream_captured(s)};
+    } left{bh, s, scope.captured};
     for (pmp_ga *ga : bh.gas)  // the batch kernels make each generation's population
         ga->init_ahead = false;
     if (!bt->graphs || bt->prof) {
@@ -2968,7 +2967,6 @@ pmp_status pmp_features(pmp_instance *inst, const uint64_t *masks, int32_t P,
     if (inst->resolve_total() != hipSuccess)
         return fail(PMP_EDEVICE, "sum of d of the instance");
     hipStream_t s = (hipStream_t)stream;
-    const DevicePool::CallScope scope(s);
     StreamCall call(s, &inst->use);
     const bool on_dev = flags & PMP_ON_DEVICE;
     const size_t W = inst->W, cells = (size_t)P * inst->m * kFeatures;
@@ -3121,7 +3119,6 @@ pmp_status model_stage(pmp_model *md, const float *x, const float *t, const floa
                        int32_t rows, bool on_dev, hipStream_t s, const float **dt,
                        const float **dw)
 {
-    const DevicePool::CallScope scope(s);
     const DevicePool::FreeScope frees(md->use.idle());  // (regrown buffers)
     if (md->cap < rows) {
         dfree(md->xf);
