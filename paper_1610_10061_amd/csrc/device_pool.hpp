@@ -196,6 +196,7 @@ public:
             e = hipMalloc(out, bytes);
         }
         if (e != hipSuccess) {
+            (void)hipGetLastError();  // (reported here, not by the next launch)
             *out = nullptr;
             return e;
         }

@@ -496,6 +496,7 @@ struct BatchHost {
     std::vector<int2> place;
     int2 *d_place = nullptr;
     size_t place_cap = 0;
+    bool tiled = false;  // the device's tables are those of the host's tiling
     StreamUse use;
 
     void drop_graphs()
@@ -909,11 +910,13 @@ hipError_t batch_tiles(BatchHost &bh, int clients)
             tile_run[x] = b;
     bh.drop_graphs();
     batch_place(bh);
+    bh.tiled = false;
     if (bh.place_cap < bh.place.size()) {
-        dfree(bh.d_place);
-        bh.place_cap = 0;
-        if (dalloc(&bh.d_place, bh.place.size()) != hipSuccess)
+        int2 *table = nullptr;  // (the former one stays if there is no memory)
+        if (dalloc(&table, bh.place.size()) != hipSuccess)
             return hipErrorOutOfMemory;
+        dfree(bh.d_place);
+        bh.d_place = table;
         bh.place_cap = bh.place.size();
     }
     bh.args.place = bh.d_place;
@@ -934,6 +937,7 @@ hipError_t batch_tiles(BatchHost &bh, int clients)
     bh.ngroups = g0[count];
     const int waves = (c0[count] + 3) / 4;  // one wave per chromosome, 4 per workgroup
     bh.want = std::max(std::max(t0[count], waves), g0[count]);
+    bh.tiled = e == hipSuccess;
     return e;
 }
 
@@ -2700,8 +2704,11 @@ pmp_status pmp_batch_autotune(pmp_batch *bt, int32_t *clients, void *stream)
         std::lock_guard<std::mutex> lock(mu);
         auto it = cache.find(key);
         if (it != cache.end()) {
-            if (batch_tiles(bh, it->second) != hipSuccess)
+            const int before = bh.clients;
+            if (batch_tiles(bh, it->second) != hipSuccess) {
+                (void)batch_tiles(bh, before);
                 return fail(PMP_EDEVICE, "batch tiling upload");
+            }
             if (clients)
                 *clients = it->second;
             return PMP_OK;
@@ -2749,6 +2756,7 @@ pmp_status pmp_batch_autotune(pmp_batch *bt, int32_t *clients, void *stream)
         }
         return least;
     };
+    const int before = bh.clients;
     int best = 0;
     float best_ms = time_it(0);
     const int commons[] = {64, 96, 128, 192, 256, 384, 512};
@@ -2769,8 +2777,11 @@ pmp_status pmp_batch_autotune(pmp_batch *bt, int32_t *clients, void *stream)
         e = batch_tiles(bh, best);
     if (e == hipSuccess)
         e = hipStreamSynchronize(s);
-    if (e != hipSuccess)
+    if (e != hipSuccess) {
+        if (!bh.tiled)
+            (void)batch_tiles(bh, before);
         return fail(PMP_EDEVICE, "batch autotune: %s", hipGetErrorString(e));
+    }
     call.waited();
     {
         std::lock_guard<std::mutex> lock(mu);
@@ -2792,6 +2803,9 @@ pmp_status pmp_batch_step(pmp_batch *bt, int32_t generations, void *stream)
     hipStream_t s = (hipStream_t)stream;
     BatchHost &bh = bt->bh;
     const CallScope scope(s);
+    if (!bh.tiled)
+        return fail(PMP_EDEVICE, "the batch's tables are not on the device (an autotune call "
+                                 "failed)");
     struct Left {  // (on every way out: this call does not wait)
         BatchHost &bh;
         hipStream_t s;
