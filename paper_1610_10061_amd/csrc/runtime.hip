@@ -409,6 +409,9 @@ struct pmp_instance {
     // and the host word its last kernel stores them to
     uint32_t *err_now = nullptr;
     uint32_t *host_err = nullptr;
+    // a waiting call failed between its evaluation and the reduction that
+    // takes its bits out of *err_now
+    std::atomic<bool> now_stale{false};
     // staging for host-pointer evaluation
     uint64_t *h_masks = nullptr;
     unsigned long long *h_fit = nullptr;
@@ -450,6 +453,24 @@ struct pmp_instance {
     }
 
     ErrOut err_out() const { return ErrOut{err_now, err, host_err}; }
+
+    // A waiting call's time between its first launch and its reduction's
+    // (taken()): left in between, the next one clears *err_now first.
+    struct Bits {
+        pmp_instance *inst;  // nullptr: a call that does not wait
+        hipError_t begin(hipStream_t s)
+        {
+            if (!inst || !inst->now_stale.exchange(false))
+                return hipSuccess;
+            return launch_zero(inst->err_now, sizeof(uint32_t), s);
+        }
+        void taken() { inst = nullptr; }
+        ~Bits()
+        {
+            if (inst)
+                inst->now_stale = true;
+        }
+    };
 
     Tables tables() const
     {
@@ -1571,8 +1592,11 @@ pmp_status pmp_hbp_eval(pmp_hbp *hp, const uint64_t *masks, int32_t P, int64_t *
     }
     a.part = hp->part;
     a.spart = dscan ? hp->spart : nullptr;
+    pmp_instance::Bits bits{async ? nullptr : inst};
+    HIP_TRY(bits.begin(s));
     HIP_TRY(launch_eval(a, s));
     HIP_TRY(launch_reduce(a, dfit, dscan, s, async ? ErrOut{} : inst->err_out()));
+    bits.taken();
     if (!on_dev) {
         HIP_TRY(hipMemcpyAsync(fitness, dfit, sizeof(int64_t) * P, hipMemcpyDeviceToHost, s));
         if (scan_total)
@@ -1748,6 +1772,8 @@ pmp_status pmp_eval_population(pmp_instance *inst, const uint64_t *masks,
     const bool folded = !async && scheme != PMP_EVAL_PER_CHROMOSOME;
     if (!async && !folded)
         HIP_TRY(launch_zero(inst->err, sizeof(uint32_t), s));
+    pmp_instance::Bits bits{folded ? inst : nullptr};
+    HIP_TRY(bits.begin(s));
 
     EvalArgs a{};
     a.t = inst->tables();
@@ -1802,6 +1828,7 @@ pmp_status pmp_eval_population(pmp_instance *inst, const uint64_t *masks,
         HIP_TRY(scheme == PMP_EVAL_PER_CLIENT ? launch_eval_per_client(a, s) : launch_eval(a, s));
         HIP_TRY(launch_reduce(a, dfit, dscan, s, folded ? inst->err_out() : ErrOut{}));
     }
+    bits.taken();
 
     if (!on_dev) {
         HIP_TRY(hipMemcpyAsync(fitness, dfit, sizeof(int64_t) * P,
@@ -1879,9 +1906,12 @@ pmp_status pmp_eval_population_noalloc(pmp_instance *inst, const uint64_t *masks
     a.tiles_i = (int32_t)ti;
     a.part = (unsigned long long *)ws;
     a.spart = scan_total ? (uint32_t *)((unsigned char *)ws + kNoAllocCells * 8) : nullptr;
+    pmp_instance::Bits bits{async ? nullptr : inst};
+    HIP_TRY(bits.begin(s));
     HIP_TRY(launch_eval(a, s));
     HIP_TRY(launch_reduce(a, (unsigned long long *)fitness, (unsigned long long *)scan_total,
                           s, async ? ErrOut{} : inst->err_out()));
+    bits.taken();
     if (async)
         return PMP_OK;
     HIP_TRY(hipStreamSynchronize(s));
