@@ -190,11 +190,16 @@ hipError_t launch_eval_per_client(const EvalArgs &a, hipStream_t s);
 int apsp_padded(int n);
 hipError_t launch_apsp_in(const int32_t *w, int64_t ldw, int n, uint32_t *D, uint32_t *wmax,
                           hipStream_t s);
-hipError_t launch_apsp_rounds(uint32_t *D, int n, hipStream_t s);
-// (d is left alone when a path length might not fit int32; the largest weight
-// goes to *host_wmax)
+// (the largest weight goes to *host_wmax; with one above apsp_most_weight(n) a
+// path length might not fit int32, and neither D nor d is written from then on)
+uint32_t apsp_most_weight(int n);
+hipError_t launch_apsp_close(uint32_t *D, int n, const uint32_t *wmax, uint32_t *host_wmax,
+                             hipStream_t s);
+int apsp_rounds(int n);
+hipError_t launch_apsp_rounds(uint32_t *D, int n, int first, int last, const uint32_t *wmax,
+                              hipStream_t s);
 hipError_t launch_apsp_out(const uint32_t *D, int n, int32_t *d, int64_t ldd,
-                           const uint32_t *wmax, uint32_t *host_wmax, hipStream_t s);
+                           const uint32_t *wmax, hipStream_t s);
 
 // Per-chromosome GA counters (summed on the host when read).
 enum GaStat : int {

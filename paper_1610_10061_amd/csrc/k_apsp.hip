@@ -107,10 +107,26 @@ __device__ __forceinline__ void close_tile(uint32_t (&v)[16], uint32_t (&pub)[2]
     }
 }
 
-__global__ __launch_bounds__(256) void k_fw_close(uint32_t *D, int ld, int kb)
+// The rounds of a call whose paths might not fit int32 (a weight above
+// `most` = (INF - 1) / (n - 1)) leave the work matrix alone: the host has
+// enqueued some or all of them when it learns that the call is refused.
+__device__ __forceinline__ bool refused(const uint32_t *wmax, uint32_t most)
+{
+    return *wmax > most;
+}
+
+// Tile (kb, kb) closed; the largest weight goes to the host word for the
+// caller's check.
+__global__ __launch_bounds__(256) void k_fw_close(uint32_t *D, int ld, int kb,
+                                                  const uint32_t *wmax, uint32_t most,
+                                                  uint32_t *host_wmax)
 {
     __shared__ uint32_t pub[2][4][kTile];
     const int lane = threadIdx.x & 63, wave = wave_id();
+    if (threadIdx.x == 0)
+        __hip_atomic_store(host_wmax, *wmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (refused(wmax, most))
+        return;
     uint32_t v[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r)
@@ -125,7 +141,9 @@ __global__ __launch_bounds__(256) void k_fw_close(uint32_t *D, int ld, int kb)
 // row kb, or of 16 rows of a tile of column kb (strips depend on themselves
 // and G only, so they are replaced in place): 8 (nb - 1) workgroups, four
 // sums per step and thread.
-__global__ __launch_bounds__(256) void k_fw_panels(uint32_t *D, int ld, int nb, int kb)
+__global__ __launch_bounds__(256) void k_fw_panels(uint32_t *D, int ld, int nb, int kb,
+                                                   const uint32_t *__restrict__ wmax,
+                                                   uint32_t most)
 {
     __shared__ __attribute__((aligned(16))) uint32_t G[kTile][kLd];  // row strips: transposed
     __shared__ __attribute__((aligned(16))) uint32_t T[kTile][20];   // T[k][strip position]
@@ -147,6 +165,8 @@ __global__ __launch_bounds__(256) void k_fw_panels(uint32_t *D, int ld, int nb, 
         T[k + 3][r] = e.w;
     }
     stage_tile(G, D, ld, kb, kb, row);
+    if (refused(wmax, most))  // (read beside the tiles)
+        return;
     __syncthreads();
     // 16 strip positions x 64: this thread's strip position and four others
     const int a = t >> 4, b = t & 15;
@@ -178,7 +198,9 @@ __global__ __launch_bounds__(256) void k_fw_panels(uint32_t *D, int ld, int nb, 
 // (kb + 1, kb + 1), the first dispatched, closes it afterwards: its waves run
 // at a higher priority than the ones they share a CU with, so that its chain
 // ends with the launch's other work and not after it.
-__global__ __launch_bounds__(256) void k_fw_rest(uint32_t *D, int ld, int nb, int kb)
+__global__ __launch_bounds__(256) void k_fw_rest(uint32_t *D, int ld, int nb, int kb,
+                                                 const uint32_t *__restrict__ wmax,
+                                                 uint32_t most)
 {
     __shared__ __attribute__((aligned(16))) uint32_t At[kTile][kLd];  // At[k][i] = D(i, kb)[i][k]
     __shared__ __attribute__((aligned(16))) uint32_t B[kTile][kLd];   // B[k][j] = D(kb, j)[k][j]
@@ -207,6 +229,8 @@ __global__ __launch_bounds__(256) void k_fw_rest(uint32_t *D, int ld, int nb, in
     }
     stage_tile(At, D, ld, ti, kb, true);
     stage_tile(B, D, ld, kb, tj, false);
+    if (refused(wmax, most))
+        return;
     __syncthreads();
 #pragma unroll 8
     for (int k = 0; k < kTile; ++k) {
@@ -288,16 +312,12 @@ __global__ __launch_bounds__(256) void k_fw_in(const int32_t *w, int64_t ldw, in
 }
 
 // Distances out: -1 for INF (no path).  Nothing is written when a path length
-// might not fit ((n - 1) * largest weight >= INF); the largest weight goes to
-// the host word for the caller's check.
+// might not fit.
 __global__ __launch_bounds__(256) void k_fw_out(const uint32_t *D, int ld, int n, int32_t *d,
                                                 int64_t ldd, const uint32_t *wmax,
-                                                uint32_t *host_wmax)
+                                                uint32_t most)
 {
-    const uint32_t mx = *wmax;
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
-        __hip_atomic_store(host_wmax, mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    if ((uint64_t)(n - 1) * mx >= kInf)
+    if (refused(wmax, most))
         return;
     const int j = (int)blockIdx.x * 256 + (int)threadIdx.x, i0 = (int)blockIdx.y * kInRows;
     if (j >= n)
@@ -319,6 +339,11 @@ int apsp_padded(int n)
     return ((n + kTile - 1) / kTile) * kTile;
 }
 
+int apsp_rounds(int n)
+{
+    return apsp_padded(n) / kTile;
+}
+
 hipError_t launch_apsp_in(const int32_t *w, int64_t ldw, int n, uint32_t *D, uint32_t *wmax,
                           hipStream_t s)
 {
@@ -328,23 +353,39 @@ hipError_t launch_apsp_in(const int32_t *w, int64_t ldw, int n, uint32_t *D, uin
     return hipGetLastError();
 }
 
-hipError_t launch_apsp_rounds(uint32_t *D, int n, hipStream_t s)
+uint32_t apsp_most_weight(int n)
+{
+    return n < 2 ? ~0u : (kInf - 1) / (uint32_t)(n - 1);
+}
+
+hipError_t launch_apsp_close(uint32_t *D, int n, const uint32_t *wmax, uint32_t *host_wmax,
+                             hipStream_t s)
+{
+    hipLaunchKernelGGL(k_fw_close, dim3(1), dim3(256), 0, s, D, apsp_padded(n), 0, wmax,
+                       apsp_most_weight(n), host_wmax);
+    return hipGetLastError();
+}
+
+hipError_t launch_apsp_rounds(uint32_t *D, int n, int first, int last, const uint32_t *wmax,
+                              hipStream_t s)
 {
     const int ld = apsp_padded(n), nb = ld / kTile;
-    hipLaunchKernelGGL(k_fw_close, dim3(1), dim3(256), 0, s, D, ld, 0);
-    for (int kb = 0; kb < nb && nb > 1; ++kb) {
-        hipLaunchKernelGGL(k_fw_panels, dim3(8 * (nb - 1)), dim3(256), 0, s, D, ld, nb, kb);
-        hipLaunchKernelGGL(k_fw_rest, dim3((nb - 1) * (nb - 1)), dim3(256), 0, s, D, ld, nb, kb);
+    const uint32_t most = apsp_most_weight(n);
+    for (int kb = first; kb < last && nb > 1; ++kb) {
+        hipLaunchKernelGGL(k_fw_panels, dim3(8 * (nb - 1)), dim3(256), 0, s, D, ld, nb, kb, wmax,
+                           most);
+        hipLaunchKernelGGL(k_fw_rest, dim3((nb - 1) * (nb - 1)), dim3(256), 0, s, D, ld, nb, kb,
+                           wmax, most);
     }
     return hipGetLastError();
 }
 
 hipError_t launch_apsp_out(const uint32_t *D, int n, int32_t *d, int64_t ldd,
-                           const uint32_t *wmax, uint32_t *host_wmax, hipStream_t s)
+                           const uint32_t *wmax, hipStream_t s)
 {
     const int ld = apsp_padded(n);
     hipLaunchKernelGGL(k_fw_out, dim3((n + 255) / 256, (n + kInRows - 1) / kInRows), dim3(256), 0,
-                       s, D, ld, n, d, ldd, wmax, host_wmax);
+                       s, D, ld, n, d, ldd, wmax, apsp_most_weight(n));
     return hipGetLastError();
 }
 

@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <climits>
 #include <cstdarg>
 #include <cstdio>
@@ -1625,6 +1626,19 @@ struct ApspCache {
         int32_t *w = nullptr, *d = nullptr;  // staging for host arguments
         size_t work_cap = 0, stage_cap = 0;
         StreamUse use;
+
+        // Waits until the largest weight is in *host_wmax: by looking at the
+        // word (an event between the launches costs an accepted call 5 to 10
+        // us), and after a millisecond, or where a kernel's store is not seen
+        // before its end, by waiting for the stream.
+        hipError_t weigh(hipStream_t s) const
+        {
+            const auto start = std::chrono::steady_clock::now();
+            while (__atomic_load_n(host_wmax, __ATOMIC_ACQUIRE) == ~0u)
+                if (std::chrono::steady_clock::now() - start > std::chrono::milliseconds(1))
+                    return hipStreamSynchronize(s);
+            return hipSuccess;
+        }
     };
     std::map<int, Dev> dev;
 };
@@ -1685,14 +1699,26 @@ pmp_status pmp_apsp(const int32_t *w, int64_t ldw, int32_t n, int32_t *d, int64_
     }
     HIP_TRY(launch_zero(b.wmax, sizeof(uint32_t), s));
     HIP_TRY(launch_apsp_in(dw, ldw_dev, n, b.work, b.wmax, s));
-    HIP_TRY(launch_apsp_rounds(b.work, n, s));
-    HIP_TRY(launch_apsp_out(b.work, n, dd, ldd_dev, b.wmax, b.host_wmax, s));
+    // With many rounds only the first are enqueued before the host looks at the
+    // largest weight (128 / rounds of them: 200 us at 16 rounds of 25, 180 us
+    // at 128 of 180, in which the host sees the weight and enqueues more), the
+    // others once the call is not refused.  Rounds of a refused call return at
+    // once, in about 4 us.  n = 1000 / 3000 / 8192, every round enqueued and
+    // run: refused calls took 0.41, 1.75 and 23 ms.
+    __atomic_store_n(b.host_wmax, ~0u, __ATOMIC_RELAXED);  // (no weight)
+    HIP_TRY(launch_apsp_close(b.work, n, b.wmax, b.host_wmax, s));
+    const int rounds = apsp_rounds(n), ahead = std::min(rounds, std::max(1, 128 / rounds));
+    HIP_TRY(launch_apsp_rounds(b.work, n, 0, ahead, b.wmax, s));
+    if (ahead < rounds) {
+        HIP_TRY(b.weigh(s));
+        if (*b.host_wmax <= apsp_most_weight(n))
+            HIP_TRY(launch_apsp_rounds(b.work, n, ahead, rounds, b.wmax, s));
+    }
+    HIP_TRY(launch_apsp_out(b.work, n, dd, ldd_dev, b.wmax, s));
     HIP_TRY(hipStreamSynchronize(s));
     call.waited();
-    // (an update never exceeds INF, so with weights too large for int32 paths
-    // the rounds have only been of no use)
     const uint32_t wmax = *b.host_wmax;
-    if ((int64_t)(n - 1) * (int64_t)wmax >= 0x7FFFFFFFll)
+    if (wmax > apsp_most_weight(n))
         return fail(PMP_EUNSUPPORTED, "path lengths may exceed int32: (n-1) * max weight = %lld",
                     (long long)(n - 1) * (long long)wmax);
     if (on_dev)
