@@ -699,14 +699,25 @@ struct pmp_ga {
         // the staging than a second workgroup does for the waits.  A generation
         // at n = 900, P = 1024: 100.4 us with 1024 workgroups, 97.8 with 512,
         // 98.5 with 256; n = 900, P = 256: 85.2 with 512, 82.9 with 256; n = 2000,
-        // p = 20, P = 512 (64 tiles): 220 with 512, 242 with 256.
-        const long target =
+        // p = 20, P = 512 (64 tiles): 220 with 512, 242 with 256.  As many times
+        // that as leave a workgroup at most 512 clients, or 640 with two per CU:
+        // whole rounds, because a workgroup or two more than a round make some
+        // CUs work twice as long.  n = m = 5000, P = 256 (32 tiles), 256 / 320 /
+        // 512 workgroups: p = 10 907, 963 and 822 us, p = 60 309, 327 and 292,
+        // p = 500 151, 157 and 150; P = 1024 (128 tiles), 512 / 1024 / 1280 / 1536:
+        // p = 10 2247, 2168, 2149 and 2139, p = 100 506, 503, 504 and 506, p = 500
+        // 244, 246, 251 and 253 (286 with 128 clients); P = 512 (64 tiles), 256 /
+        // 512 / 640 / 1024: n = 5000, m = 1000, p = 20 324, 292, 305 and 292, m = 200,
+        // p = 1 173, 146, 158 and 145.
+        const long round =
             std::max(1, env_int("PMP_MUTANT_WORKGROUPS", (tiles_c < 64 ? 1 : 2) * device_cus()));
-        int ti = (int)std::max(1L, std::min((long)n, target / std::max(1L, tiles_c)));
-        // at most 512 clients per workgroup (n = 5000: 286 us a generation with
-        // 128, 265 with 256, 251 with 512, 253 with 1024)
-        ti = std::max(ti, (n + 511) / 512);
-        int cpb = (n + ti - 1) / ti;
+        int ti = 1, cpb = n;
+        for (long k = 1; ti < n; ++k) {
+            ti = (int)std::max(1L, std::min((long)n, k * round / std::max(1L, tiles_c)));
+            cpb = (n + ti - 1) / ti;
+            if (cpb <= (tiles_c < 64 ? 512 : 640))
+                break;
+        }
         cpb = std::max(cpb, this->cpb);
         cpb = ((cpb + 3) / 4) * 4;
         ti = (n + cpb - 1) / cpb;
