@@ -347,19 +347,56 @@ int clients_per_block(int n, int P, int m, int p, int W, bool reduced = false,
     return (int)cpb;
 }
 
+// 64-entry chunks that the wave of a client walks until each of its 64
+// chromosomes has met an open facility: about (ln 64 + 0.58) m / p entries.
+double walk_chunks(int m, int p)
+{
+    return std::ceil(std::min((double)(m - p + 1), 4.74 * m / p) / 64.0);
+}
+
 // Clients per workgroup of a GA run's population evaluation: the rule above,
 // but no more client tiles than the stage that adds up their partial sums
-// loads in one round, 16 (a row of 16 lanes per chromosome) when the crossover
-// stages are fused with their evaluations, else 64.  A generation at n = 900,
-// P = 64: 114 us with the rule's 4 clients, 71 with 64; n = 400, P = 256: 99
-// and 86 (with 32); n = 1500, P = 256 (not fused): 123 and 112 (with 32).
+// loads in a few rounds of 16 (a row of 16 lanes per chromosome) when the
+// crossover stages are fused with their evaluations, else of 64.  A round
+// costs about 2.4 us, a client 0.24 us per chunk of its walk and wave, so that
+// r rounds cost the least at r = sqrt(0.1 chunks n / (tiles of a round x
+// waves)); more workgroups than CUs shorten no walk.  A generation at n = 900,
+// P = 64, p = 90: 114 us with the rule's 4 clients, 71 with 64 (one round);
+// n = 400, P = 256: 99 and 86 (with 32); n = 1500, P = 256 (not fused): 123 and
+// 112 (with 32).  One round and r of them: n = m = 8000, p = 8, P = 64 (4 rounds)
+// 1302 and 624 us, n = m = 5000, p = 10, P = 64 (4) 532 and 344, p = 100 (2) 162
+// and 144; fused: n = 8000, m = 1000, p = 3, P = 64 (9) 468 and 272, n = m = 1000,
+// p = 5, P = 64 (3) 123 and 116, n = 5000, m = 200, p = 1, P = 512 (2) 144 and 131.
 int ga_clients_per_block(int n, int P, int m, int p, int W, int waves, bool fused)
 {
     const int cpb = clients_per_block(n, P, m, p, W, false, waves);
     if (env_int("PMP_CLIENTS_PER_BLOCK", 0) > 0)
         return cpb;
-    const int most = fused ? 16 : 64;
-    const int least = (n + most - 1) / most;
+    const int round = fused ? 16 : 64;
+    const long tiles_c = (P + kEvalTile - 1) / kEvalTile;
+    const double best = std::sqrt(0.1 * walk_chunks(m, p) * n / ((double)round * waves));
+    const long fit = device_cus() / (tiles_c * round);  // rounds that leave a CU each
+    const long most = round * std::max(1L, std::min(fit, (long)std::ceil(best)));
+    const int least = (int)((n + most - 1) / most);
+    return std::max(cpb, (least + waves - 1) / waves * waves);
+}
+
+// The same of a run in a batch of `beside` chromosome tiles in all, whose
+// stages (a wave per chromosome) add up 64 tiles a round: a CU per workgroup
+// while the batch leaves the chip room, never fewer tiles than a round of the
+// run alone.  A generation with one round of the run alone and with this:
+// one run of n = 8000, m = 1000, p = 3, P = 64 1924 and 291 us, two of n = m = 1000,
+// p = 5, P = 128 299 and 174, eight of n = m = 400, p = 20, P = 64 144 and 137; 16
+// of n = m = 1000, p = 4, P = 256 fill the chip (795; 867 with 32 tiles each).
+int batch_clients_per_block(int n, int P, int m, int p, int W, int waves, bool fused, long beside)
+{
+    const int cpb = clients_per_block(n, P, m, p, W, false, waves);
+    if (env_int("PMP_CLIENTS_PER_BLOCK", 0) > 0)
+        return cpb;
+    const double best = std::sqrt(0.1 * walk_chunks(m, p) * n / (64.0 * waves));
+    const long most = std::max(fused ? 16L : 64L,
+                               std::min(device_cus() / beside, 64 * (long)std::ceil(best)));
+    const int least = (int)((n + most - 1) / most);
     return std::max(cpb, (least + waves - 1) / waves * waves);
 }
 
@@ -565,8 +602,10 @@ struct pmp_ga {
     pmp_instance *inst = nullptr;
     pmp_ga_params prm{};
     int NB = 0, lg = 0, X = 0, Y = 0, TI = 0, cpb = 0;
+    bool tuned = false;           // cpb was measured, not taken by rule
     bool fused = true;            // crossover stages fused with their evaluations
     int fcpb = 0, fTI = 0;        // client tiles of the fused launches
+    int part_ti = 0;              // client tiles that the partial sums have room for
     int waves = kEvalWaves;       // waves per workgroup of the population's evaluation
     int spec_waves = kEvalWaves;  // and of the mutants' evaluation
     uint64_t *cur[2] = {nullptr, nullptr}, *off[2] = {nullptr, nullptr};
@@ -607,6 +646,7 @@ struct pmp_ga {
         parts.add(&spart, cells);
         parts.add(&part2, cells);
         parts.add(&spart2, cells);
+        part_ti = tiles;
         return parts.carve();
     }
     bool persistent = false;  // one persistent launch per pmp_ga_step call
@@ -864,8 +904,7 @@ EvalArgs ga_eval_args(const pmp_ga *ga, const GaArgs &g, int buf);
 // further chunk costs half a first one.
 double client_cost(const pmp_instance *inst)
 {
-    const double longest = std::min((double)inst->K, 4.74 * inst->m / inst->p);
-    return 1.0 + 0.5 * (std::ceil(longest / 64.0) - 1.0);
+    return 1.0 + 0.5 * (walk_chunks(inst->m, inst->p) - 1.0);
 }
 
 // The evaluation's workgroups in launch order: units of one client tile (its
@@ -925,7 +964,7 @@ hipError_t batch_tiles(BatchHost &bh, int clients)
     for (int b = 0; b < count; ++b) {
         BatchItem &it = bh.items[b];
         const pmp_ga *ga = bh.gas[b];
-        const int n = ga->inst->n, cap = std::max(ga->TI, ga->fTI);
+        const int n = ga->inst->n, cap = ga->part_ti;
         if (clients > 0) {
             const double cost = client_cost(ga->inst);
             const int own = cost > 1.0 ? std::max(16, (int)(clients / cost) / 16 * 16) : clients;
@@ -982,6 +1021,9 @@ hipError_t batch_build(BatchHost &bh, pmp_ga *const *gas, int count)
     bh.base_cpb.assign((size_t)count, 0);
     int32_t *c0 = bh.prefix.data(), *g0 = c0 + 2 * (count + 1);
     int max_S = 0, max_w2 = 2;
+    long beside = 0;
+    for (int b = 0; b < count; ++b)
+        beside += (gas[b]->prm.population + kEvalTile - 1) / kEvalTile;
     for (int b = 0; b < count; ++b) {
         pmp_ga *ga = gas[b];
         BatchItem &it = bh.items[b];
@@ -993,7 +1035,12 @@ hipError_t batch_build(BatchHost &bh, pmp_ga *const *gas, int count)
         // clients per workgroup (fewer client tiles, so the partial sums
         // still fit).
         const int scale = 16 / std::max(1, std::min(16, ga->waves));
-        bh.base_cpb[b] = ga->cpb * scale;
+        const pmp_instance *in = ga->inst;
+        const int cpb = ga->tuned ? ga->cpb
+                                  : batch_clients_per_block(in->n, ga->prm.population, in->m,
+                                                            in->p, in->W, ga->waves, ga->fused,
+                                                            beside);
+        bh.base_cpb[b] = cpb * scale;
         it.X = ga->xstages();
         it.S = it.X + ga->Y;
         it.fb = ga->final_buf();
@@ -1005,7 +1052,7 @@ hipError_t batch_build(BatchHost &bh, pmp_ga *const *gas, int count)
     // a run's tile count is at most its partial-sum capacity in any tiling
     bh.max_tiles = 0;
     for (int b = 0; b < count; ++b)
-        bh.max_tiles += bh.items[b].e.tiles_c * std::max(gas[b]->TI, gas[b]->fTI);
+        bh.max_tiles += bh.items[b].e.tiles_c * gas[b]->part_ti;
     bh.runs.assign((size_t)c0[count] + g0[count] + bh.max_tiles, 0);
     for (int b = 0; b < count; ++b) {
         for (int x = c0[b]; x < c0[b + 1]; ++x)
@@ -2041,6 +2088,10 @@ pmp_status pmp_ga_create(pmp_instance *inst, const pmp_ga_params *prm,
     ga->TI = (inst->n + ga->cpb - 1) / ga->cpb;
     ga->fcpb = fused_clients_per_block(inst->n, P);
     ga->fTI = (inst->n + ga->fcpb - 1) / ga->fcpb;
+    const int batch_cpb =
+        batch_clients_per_block(inst->n, P, inst->m, inst->p, inst->W, ga->waves, ga->fused,
+                                (P + kEvalTile - 1) / kEvalTile);
+    const int batch_ti = (inst->n + batch_cpb - 1) / batch_cpb;
     const size_t W = inst->W, PW = (size_t)P * W;
     for (int k = 0; k < 2; ++k) {
         ga->arena.add(&ga->cur[k], PW);
@@ -2061,7 +2112,7 @@ pmp_status pmp_ga_create(pmp_instance *inst, const pmp_ga_params *prm,
     if (!binom.empty())
         ga->arena.add(&ga->binom, binom.size());
     const bool bad = ga->arena.carve() != hipSuccess ||
-                     ga->carve_parts(std::max(ga->TI, ga->fTI)) != hipSuccess;
+                     ga->carve_parts(std::max({ga->TI, ga->fTI, batch_ti})) != hipSuccess;
     if (bad) {
         pmp_ga_destroy(ga);
         return fail(PMP_ENOMEM, "GA buffers for P=%d", P);
@@ -2693,6 +2744,7 @@ pmp_status pmp_ga_autotune(pmp_ga *ga, int32_t *clients, int32_t *waves, void *s
         if (ga->carve_parts(std::max(ti, ga->fTI)) != hipSuccess)
             return fail(PMP_ENOMEM, "GA partial sums for %d client tiles", ti);
         ga->cpb = best;
+        ga->tuned = true;
         ga->TI = ti;
         if (ga->self) {
             ga->self->release(ga->use.idle());

@@ -4,15 +4,18 @@ import hip_stub
 
 
 def test_failed_autotune_keeps_the_tables(tmp_path):
-    # n = 900, p = 20 alone: 64 clients a workgroup; common counts give it more
-    # tiles, whose launch table is larger
+    # 16 runs with long walks fill the chip with 16 client tiles each; common
+    # counts give them more tiles, whose launch table is larger
     hip_stub.run(tmp_path, """
+x = instance(1000, 1000, 4)
+
+
 def evals():
     return [r[2] for r in log("launch") if "k_batch_eval" in r[1]]
 
 
 def stepped():
-    b = batch([ga(instance(900, 900, 20), 64)])
+    b = batch([ga(x, 256) for _ in range(16)])
     clear()
     ok(pmp.pmp_batch_step(b, 1, None))
     return b, evals()

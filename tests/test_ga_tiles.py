@@ -39,3 +39,40 @@ def filled(workgroups, round):
 def test_mutants_fill_whole_rounds(evals, n, m, p, P, NT, round):
     w = evals(n, m, p, P, NT)[-1]
     assert filled(w, round) > 0.85, w
+
+
+# n, m, p, P, NT, client tiles that the next stage adds up in a round (16: at
+# most 1024 facilities), rounds
+@pytest.mark.parametrize("n,m,p,P,NT,tiles,rounds", [
+    # walks of a chunk or two, or as many workgroups as CUs in a round
+    (900, 900, 90, 64, 64, 16, 1), (400, 400, 20, 256, 256, 16, 1),
+    (1500, 1500, 75, 256, 256, 64, 1), (5000, 5000, 10, 256, 256, 64, 1),
+    (1000, 1000, 5, 1024, 256, 16, 1),
+    # long walks of small populations
+    (8000, 8000, 8, 64, 64, 64, 4), (5000, 5000, 10, 64, 64, 64, 3),
+    (5000, 5000, 100, 64, 64, 64, 2), (8000, 1000, 3, 64, 64, 16, 8),
+    (1000, 1000, 5, 64, 64, 16, 2), (5000, 500, 3, 128, 128, 16, 4),
+])
+def test_population_tiles_by_rounds(evals, n, m, p, P, NT, tiles, rounds):
+    # (of client tiles after their clients are rounded up to whole waves)
+    w = evals(n, m, p, P, NT)[0]
+    assert -(-w // (P // 64) // tiles) == rounds, w
+
+
+# n, m, p, P, NT, runs, client tiles of each: one round where the runs fill the
+# chip, as many as alone where one run is all there is
+@pytest.mark.parametrize("n,m,p,P,NT,runs,tiles", [
+    (1000, 1000, 4, 256, 64, 16, 16), (8000, 8000, 8, 64, 64, 1, 250),
+    (8000, 1000, 3, 64, 64, 1, 250),
+])
+def test_batch_tiles_by_rounds(tmp_path, n, m, p, P, NT, runs, tiles):
+    out = hip_stub.run(tmp_path, f"""
+stub.stub_quiet(1)
+b = batch([ga(instance({n}, {m}, {p}), {P}, {NT}) for _ in range({runs})])
+stub.stub_quiet(0)
+clear()
+ok(pmp.pmp_batch_step(b, 1, None))
+print(*[r[2] for r in log("launch") if "k_batch_eval" in r[1]])
+""")
+    want = runs * (P // 64) * tiles
+    assert all(want <= int(x) < want + 8 for x in out.split()), out
