@@ -76,3 +76,24 @@ print(*[r[2] for r in log("launch") if "k_batch_eval" in r[1]])
 """)
     want = runs * (P // 64) * tiles
     assert all(want <= int(x) < want + 8 for x in out.split()), out
+
+
+# n, p, P, runs: few client tiles of many chromosome tiles
+@pytest.mark.parametrize("n,p,P,runs", [
+    (100, 10, 16384, 1), (100, 10, 4096, 2), (200, 20, 8192, 3), (64, 5, 8192, 4),
+    (100, 10, 64, 1), (500, 50, 1024, 2),
+])
+def test_batch_uses_every_xcd(tmp_path, n, p, P, runs):
+    """The launch is eight lists of workgroups, one per XCD, padded to the
+    longest: with equal runs they are of about one length."""
+    out = hip_stub.run(tmp_path, f"""
+stub.stub_quiet(1)
+b = batch([ga(instance({n}, {n}, {p}), {P}) for _ in range({runs})])
+stub.stub_quiet(0)
+clear()
+ok(pmp.pmp_batch_step(b, 1, None))
+print(*[r[2] for r in log("launch") if "k_batch_eval" in r[1]])
+""", {"PMP_BATCH_CLIENTS": str(n)})
+    # (one client tile a run)
+    tiles = runs * (P // 64)
+    assert all(tiles <= int(x) <= 1.125 * tiles + 8 for x in out.split()), (out, tiles)
