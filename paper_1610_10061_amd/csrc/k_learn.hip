@@ -596,6 +596,7 @@ __global__ __launch_bounds__(64 * kMlpWaves) void k_prop_score(LearnArgs A, int 
 // atomic per entry 16 us for L = 50, 145 us for L = 500; the one launch takes
 // 31 and 38 us (100 MB of d: 3.2 TB/s).
 constexpr int kStaticThreads = 1024;
+constexpr size_t kStaticParts = sizeof(unsigned long long) * kStaticThreads;  // static LDS
 
 __global__ __launch_bounds__(kStaticThreads) void k_static(
     const int32_t *__restrict__ d, int64_t ld, int n, int m, int near, int slices,
@@ -1248,8 +1249,9 @@ hipError_t launch_static_sums(const int32_t *d, int64_t ld, int n, int m, const 
     near = std::max(near, (int)std::max<int64_t>((n + 65534) / 65535, (entries >> 30) + 1));
     near = std::min(near, n);
     const int rows_per = (n + near - 1) / near;
+    // (64 KB without asking for more: the counts and the columns' parts together)
     const size_t lds = sizeof(uint32_t) * (size_t)((m + 1) / 2);
-    if (lds > 65536) {
+    if (lds + kStaticParts > 65536) {
         const hipError_t e =
             hipFuncSetAttribute(reinterpret_cast<const void *>(k_static),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
