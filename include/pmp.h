@@ -20,8 +20,15 @@
  *    results are in host memory.  PMP_ASYNC (with PMP_ON_DEVICE) skips the
  *    final stream wait: errors found on the device are then kept in the
  *    instance's error word until pmp_instance_check().
- *  - Handles own all device memory they allocate until *_destroy.  Input
- *    buffers are borrowed for the duration of the call (for asynchronous
+ *  - Handles own all device memory they allocate until *_destroy, which gives
+ *    it to the driver, or, when every call that used the handle has been
+ *    waited for (by a call that waits on the same stream), keeps it for later
+ *    handles: at most PMP_DEVICE_CACHE_MB megabytes per device (environment,
+ *    read once; default 1024, 0 keeps nothing).  Kept memory goes back to the
+ *    driver when the library itself runs out, in pmp_device_cache_trim(), and
+ *    after ten seconds without use, though only at the library's next
+ *    allocation or free.
+ *  - Input buffers are borrowed for the duration of the call (for asynchronous
  *    calls: until the enqueued work has run); outputs go to caller buffers.
  *  - Handles are not thread-safe: calls on one handle must not overlap.
  */
@@ -587,6 +594,11 @@ PMP_API pmp_status pmp_ga_set_model(pmp_ga *ga, pmp_model *model,
 PMP_API pmp_status pmp_ga_replay(pmp_ga *ga, int32_t *rows, uint16_t *x, float *target,
                                  float *weight, int32_t *swap, int64_t *delta,
                                  float *scores, void *stream);
+
+/* Gives the driver all device memory kept for later handles (see the
+ * conventions above), on every device: for a program that goes on with other
+ * work, or whose other allocations need the room. */
+PMP_API pmp_status pmp_device_cache_trim(void);
 
 PMP_API const char *pmp_status_str(pmp_status s);
 PMP_API const char *pmp_last_error(void);

@@ -30,7 +30,7 @@ __all__ = [
     "pmp_model_set", "pmp_model_forward", "pmp_model_grad", "pmp_model_train",
     "pmp_model_destroy", "pmp_ga_set_model", "pmp_ga_replay", "pmp_exhaustive",
     "pmp_apsp", "pmp_hbp_reduce", "pmp_hbp_info", "pmp_hbp_terms", "pmp_hbp_eval",
-    "pmp_hbp_destroy", "Instance", "GA", "Hbp",
+    "pmp_hbp_destroy", "pmp_device_cache_trim", "Instance", "GA", "Hbp",
     "Batch", "Model", "LearnParams", "EXPORTS", "MLP_PARAMS",
 ]
 
@@ -58,7 +58,7 @@ EXPORTS = [
     "pmp_ga_set_model", "pmp_ga_replay", "pmp_exhaustive", "pmp_apsp",
     "pmp_hbp_reduce", "pmp_hbp_info", "pmp_hbp_terms", "pmp_hbp_eval", "pmp_hbp_destroy",
     "pmp_eval_population_noalloc", "pmp_batch_profile", "pmp_batch_profile_read",
-    "pmp_batch_autotune",
+    "pmp_batch_autotune", "pmp_device_cache_trim",
 ]
 
 FEATURES = 16
@@ -345,6 +345,11 @@ def pmp_instance_check(inst, stream=None):
 
 def pmp_instance_destroy(inst):
     lib().pmp_instance_destroy(inst)
+
+
+def pmp_device_cache_trim():
+    """Gives the driver all device memory kept from destroyed handles."""
+    _check(lib().pmp_device_cache_trim(), "pmp_device_cache_trim")
 
 
 def pmp_ga_create(inst, population, group_size, generations, seed,

@@ -12,11 +12,12 @@
 //    still run go to hipFree, which waits.  (A wait for the whole device here
 //    instead would not be allowed while any stream of the process is being
 //    captured, by whatever thread, and would spoil that capture.)
-//  - The cache holds at most PMP_DEVICE_CACHE_MB (default 1024) per device;
-//    past that the block freed longest ago goes back to the driver, as does
-//    every block that nobody has asked for in kMaxIdle.  When the driver is
-//    out of memory everything cached goes back and the allocation is tried
-//    again.
+//  - The cache holds at most PMP_DEVICE_CACHE_MB (default 1024, 0: nothing)
+//    per device; past that the block freed longest ago goes back to the driver.
+//    A block that nobody has asked for in kMaxIdle goes back at the next
+//    allocation or free of the library (there is no thread that would do it in
+//    between), everything goes back at trim() (pmp_device_cache_trim) and when
+//    the driver is out of memory, whereupon the allocation is tried again.
 //  - While the stream of the calling entry point is being captured (every
 //    entry point that takes a stream opens a CallScope) the cache is left
 //    alone: the driver is asked, as without one, and decides.
@@ -175,6 +176,7 @@ public:
         hipError_t e = hipGetDevice(&dev);
         if (e != hipSuccess)
             return e;
+        std::list<Block> idle;
         if (!CallScope::direct()) {
             std::lock_guard<std::mutex> lock(mu_);
             auto best = cached_.end();
@@ -187,11 +189,14 @@ public:
                 live_[best->p] = {best->bytes, dev};
                 held_[dev] -= best->bytes;
                 cached_.erase(best);
-                return hipSuccess;
             }
+            expire(Clock::now(), idle);
         }
+        to_driver(idle);
+        if (*out)
+            return hipSuccess;
         e = hipMalloc(out, bytes);
-        if (e == hipErrorOutOfMemory && !CallScope::direct() && give_back(dev)) {
+        if (e == hipErrorOutOfMemory && !CallScope::direct() && trim(dev)) {
             (void)hipGetLastError();
             e = hipMalloc(out, bytes);
         }
@@ -228,17 +233,33 @@ public:
             const Clock::time_point now = Clock::now();
             cached_.push_back({p, b.bytes, b.dev, now});  // (oldest first)
             held_[b.dev] += b.bytes;
-            for (auto it = cached_.begin(); it != cached_.end();) {
+            expire(now, out);
+            for (auto it = cached_.begin(); held_[b.dev] > limit_;) {
                 const auto next = std::next(it);
-                if (now - it->since > kMaxIdle || (it->dev == b.dev && held_[b.dev] > limit_)) {
-                    held_[it->dev] -= it->bytes;
-                    out.splice(out.end(), cached_, it);
-                }
+                if (it->dev == b.dev)
+                    drop(it, out);
                 it = next;
             }
         }
-        for (const Block &o : out)
-            (void)hipFree(o.p);
+        to_driver(out);
+    }
+
+    // Every cached block of a device (dev < 0: of all) to the driver; false if
+    // there was none.
+    bool trim(int dev = -1)
+    {
+        std::list<Block> out;
+        {
+            std::lock_guard<std::mutex> lock(mu_);
+            for (auto it = cached_.begin(); it != cached_.end();) {
+                const auto next = std::next(it);
+                if (dev < 0 || it->dev == dev)
+                    drop(it, out);
+                it = next;
+            }
+        }
+        to_driver(out);
+        return !out.empty();
     }
 
 private:
@@ -267,23 +288,21 @@ private:
         return k;
     }
 
-    // Every cached block of a device to the driver; false if there was none.
-    bool give_back(int dev)
+    // A cached block to `out` (with mu_ held; to_driver gives it back after).
+    void drop(std::list<Block>::iterator it, std::list<Block> &out)
     {
-        std::list<Block> out;
-        {
-            std::lock_guard<std::mutex> lock(mu_);
-            for (auto it = cached_.begin(); it != cached_.end();) {
-                const auto next = std::next(it);
-                if (it->dev == dev)
-                    out.splice(out.end(), cached_, it);
-                it = next;
-            }
-            held_[dev] = 0;
-        }
-        for (const Block &o : out)
-            (void)hipFree(o.p);
-        return !out.empty();
+        held_[it->dev] -= it->bytes;
+        out.splice(out.end(), cached_, it);
+    }
+    void expire(Clock::time_point now, std::list<Block> &out)
+    {
+        while (!cached_.empty() && now - cached_.front().since > kMaxIdle)
+            drop(cached_.begin(), out);
+    }
+    static void to_driver(const std::list<Block> &blocks)
+    {
+        for (const Block &b : blocks)
+            (void)hipFree(b.p);
     }
 
     std::mutex mu_;

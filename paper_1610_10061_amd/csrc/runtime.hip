@@ -1215,6 +1215,12 @@ const char *pmp_status_str(pmp_status s)
 
 const char *pmp_last_error(void) { return g_last_error.c_str(); }
 
+pmp_status pmp_device_cache_trim(void)
+{
+    (void)DevicePool::get().trim();
+    return PMP_OK;
+}
+
 void pmp_instance_destroy(pmp_instance *inst)
 {
     if (!inst)
