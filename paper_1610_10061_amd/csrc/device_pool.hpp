@@ -29,8 +29,10 @@
 #include <chrono>
 #include <cstdlib>
 #include <list>
+#include <map>
 #include <mutex>
 #include <unordered_map>
+#include <utility>
 
 namespace pmp {
 
@@ -179,16 +181,13 @@ public:
         std::list<Block> idle;
         if (!CallScope::direct()) {
             std::lock_guard<std::mutex> lock(mu_);
-            auto best = cached_.end();
-            for (auto it = cached_.begin(); it != cached_.end(); ++it)
-                if (it->dev == dev && it->bytes >= bytes && it->bytes <= bytes + bytes / 4 + 4096 &&
-                    (best == cached_.end() || it->bytes < best->bytes))
-                    best = it;
-            if (best != cached_.end()) {
-                *out = best->p;
-                live_[best->p] = {best->bytes, dev};
-                held_[dev] -= best->bytes;
-                cached_.erase(best);
+            const auto fit = by_size_.lower_bound({dev, bytes});  // the smallest that holds it
+            if (fit != by_size_.end() && fit->first.first == dev &&
+                fit->first.second <= bytes + bytes / 4 + 4096) {
+                std::list<Block> taken;
+                *out = fit->second->p;
+                live_[*out] = {fit->second->bytes, dev};
+                drop(fit->second, taken);
             }
             expire(Clock::now(), idle);
         }
@@ -231,7 +230,8 @@ public:
         {
             std::lock_guard<std::mutex> lock(mu_);
             const Clock::time_point now = Clock::now();
-            cached_.push_back({p, b.bytes, b.dev, now});  // (oldest first)
+            const auto at = cached_.insert(cached_.end(), {p, b.bytes, b.dev, now, {}});
+            at->place = by_size_.insert({{b.dev, b.bytes}, at});
             held_[b.dev] += b.bytes;
             expire(now, out);
             for (auto it = cached_.begin(); held_[b.dev] > limit_;) {
@@ -269,11 +269,14 @@ private:
         size_t bytes;
         int dev;
     };
+    struct Block;
+    using BySize = std::multimap<std::pair<int, size_t>, std::list<Block>::iterator>;
     struct Block {
         void *p;
         size_t bytes;
         int dev;
         Clock::time_point since;
+        BySize::iterator place;
     };
 
     DevicePool()
@@ -292,6 +295,7 @@ private:
     void drop(std::list<Block>::iterator it, std::list<Block> &out)
     {
         held_[it->dev] -= it->bytes;
+        by_size_.erase(it->place);
         out.splice(out.end(), cached_, it);
     }
     void expire(Clock::time_point now, std::list<Block> &out)
@@ -308,6 +312,7 @@ private:
     std::mutex mu_;
     size_t limit_ = 0;
     std::list<Block> cached_;                // oldest first
+    BySize by_size_;                         // the same by device and size
     std::unordered_map<int, size_t> held_;   // cached bytes by device
     std::unordered_map<void *, Live> live_;  // blocks in use
 };

@@ -91,3 +91,23 @@ ok(pmp.pmp_preprocess(big, 300, 3000, 300, 5, ON_DEVICE, None, C.byref(out)))
 def test_binding():
     import paper_1610_10061_amd as pm
     pm.pmp_device_cache_trim()
+
+
+def test_many_blocks(run):
+    """Taking and keeping a block costs about the same however many are kept."""
+    run("""
+stub.stub_quiet(1)
+d = buf(4 * 40 * 40)
+
+
+def again(count):  # us per instance, made of kept blocks and destroyed
+    for rep in range(2):
+        t = time.perf_counter()
+        for x in [instance(8 + k % 32, 40, 5, d=d) for k in range(count)]:
+            pmp.pmp_instance_destroy(x)
+    return (time.perf_counter() - t) / count
+
+
+few, many = again(1000), again(20000)
+assert many < 5 * few, (few, many)
+""")
