@@ -1786,20 +1786,18 @@ pmp_status pmp_apsp(const int32_t *w, int64_t ldw, int32_t n, int32_t *d, int64_
     }
     HIP_TRY(launch_zero(b.wmax, sizeof(uint32_t), s));
     HIP_TRY(launch_apsp_in(dw, ldw_dev, n, b.work, b.wmax, s));
-    // With many rounds only the first are enqueued before the host looks at the
-    // largest weight (128 / rounds of them: 200 us at 16 rounds of 25, 180 us
-    // at 128 of 180, in which the host sees the weight and enqueues more), the
-    // others once the call is not refused.  Rounds of a refused call return at
-    // once, in about 4 us.  n = 1000 / 3000 / 8192, every round enqueued and
-    // run: refused calls took 0.41, 1.75 and 23 ms.
+    // The host looks at the largest weight while the first diagonal tile is
+    // closed and the first round runs, in time to enqueue an accepted call's
+    // other rounds before the device is through with these.  A refused call's
+    // first round returns at once.
     __atomic_store_n(b.host_wmax, ~0u, __ATOMIC_RELAXED);  // (no weight)
     HIP_TRY(launch_apsp_close(b.work, n, b.wmax, b.host_wmax, s));
-    const int rounds = apsp_rounds(n), ahead = std::min(rounds, std::max(1, 128 / rounds));
-    HIP_TRY(launch_apsp_rounds(b.work, n, 0, ahead, b.wmax, s));
-    if (ahead < rounds) {
+    const int rounds = apsp_rounds(n);
+    if (rounds > 1) {
+        HIP_TRY(launch_apsp_rounds(b.work, n, 0, 1, b.wmax, s));
         HIP_TRY(b.weigh(s));
         if (*b.host_wmax <= apsp_most_weight(n))
-            HIP_TRY(launch_apsp_rounds(b.work, n, ahead, rounds, b.wmax, s));
+            HIP_TRY(launch_apsp_rounds(b.work, n, 1, rounds, b.wmax, s));
     }
     HIP_TRY(launch_apsp_out(b.work, n, dd, ldd_dev, b.wmax, s));
     HIP_TRY(hipStreamSynchronize(s));
