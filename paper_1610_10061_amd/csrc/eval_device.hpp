@@ -339,27 +339,6 @@ constexpr int eval_stage_words()
     return kEvalTile * (WD + 1);
 }
 
-// Evaluate chromosome tile tc (64 chromosomes) on client tile ti and store
-// the tile's partial sums.  Called by a whole workgroup of NV waves (each
-// walks every NV-th client of the tile; more waves share one staged tile,
-// so more of them are resident per CU and each walks fewer clients);
-// smask holds eval_stage_words<WD>() words (8-byte aligned), sred
-// 2 * NV * 64 words.
-//
-// R: the walk tables of the reduced polynomial (k_hbp.hip) instead of the
-// instance's: row i stops at position K_i - 1 at the latest (a.rlen) and
-// the value read there is the int64 running sum a.e64.  The stop is made
-// with no extra work in the walk: the last position's lane takes a row of
-// all ones, as if its facility were open in every chromosome.
-//
-// H (short scans, not with R): a wave walks its clients two at a time, the
-// first 32 entries of each row in one chunk (first_open2); the few rows
-// whose first open facility lies past entry 31 finish in walk_rest.
-//
-// PRE: the caller has already staged the tile's masks in smask (rows at
-// stride WD + 1, zero past 2W words) and the chromosomes' active flags in
-// sact, and synchronised the workgroup (the stage steps fused with the
-// evaluation make the offspring right there).
 // Whether the single-client walk reads its first chunks by first_open_lds.
 // Not for chromosomes of up to four words: their few facilities send most
 // clients on to a second chunk, and handing over between the two numberings
@@ -402,6 +381,29 @@ __device__ __forceinline__ FirstChunk eval_first_chunk(const EvalArgs &a, int ti
     return fc;
 }
 
+static __device__ const unsigned long long kNoStopFlag = 0ull;
+
+// Evaluate chromosome tile tc (64 chromosomes) on client tile ti and store
+// the tile's partial sums.  Called by a whole workgroup of NV waves (each
+// walks every NV-th client of the tile; more waves share one staged tile,
+// so more of them are resident per CU and each walks fewer clients);
+// smask holds eval_stage_words<WD>() words (8-byte aligned), sred
+// 2 * NV * 64 words.
+//
+// R: the walk tables of the reduced polynomial (k_hbp.hip) instead of the
+// instance's: row i stops at position K_i - 1 at the latest (a.rlen) and
+// the value read there is the int64 running sum a.e64.  The stop is made
+// with no extra work in the walk: the last position's lane takes a row of
+// all ones, as if its facility were open in every chromosome.
+//
+// H (short scans, not with R): a wave walks its clients two at a time, the
+// first 32 entries of each row in one chunk (first_open2); the few rows
+// whose first open facility lies past entry 31 finish in walk_rest.
+//
+// PRE: the caller has already staged the tile's masks in smask (rows at
+// stride WD + 1, zero past 2W words) and the chromosomes' active flags in
+// sact, and synchronised the workgroup (the stage steps fused with the
+// evaluation make the offspring right there).
 //
 // GT: the tile's facility-major copy is in device memory (a.tg; chromosomes
 // wider than the LDS staging allows), made and checked by launch_tile_major;
@@ -410,8 +412,6 @@ __device__ __forceinline__ FirstChunk eval_first_chunk(const EvalArgs &a, int ti
 // issues the loads and leaves with the stop test, so that no branch comes
 // before the loads (the compiler then issues them, and the kernel arguments
 // they need, in one round each).
-static __device__ const unsigned long long kNoStopFlag = 0ull;
-
 template <int WD, bool R = false, bool H = false, int NV = kEvalWaves, bool PRE = false,
           bool GT = false>
 __device__ __forceinline__ void eval_tile(const EvalArgs &a, int ti, int tc,
@@ -512,7 +512,7 @@ __device__ __forceinline__ void eval_tile(const EvalArgs &a, int ti, int tc,
     if constexpr (!GT)
         __syncthreads();
 
-    // Facility-major copy: wave v turns the tile's 64-bit words v, v + 4, ...
+    // Facility-major copy: wave v turns the tile's 64-bit words v, v + NV, ...
     // (one row per lane) into T[64 w + f], f = 0..63, by one transpose each,
     // in place once every wave has read its rows.
     const uint64_t *sT = nullptr;
