@@ -659,8 +659,8 @@ def bench_apsp(args):
     Floyd-Warshall): n = 900 with 16200 edges (G900), n = 2000 with 8000
     edges (the largest batch graph) and n = 4096 with 16384 edges.  Wall time
     of pmp_apsp on device buffers (median of 5 after a warm-up); the
-    algorithmic work is n^3 min-plus updates of one add and one min each,
-    against the int32 vector ALU peak.  Results are checked against the
+    algorithmic work is n^3 min-plus updates of an add and half a v_min3
+    (which takes two sums at once), against the int32 vector ALU peak.  Results are checked against the
     input generator's Dijkstra distances (n <= 2000); the CPU baseline is
     the oracle's Floyd-Warshall at n = 900."""
     import numpy as np
@@ -668,7 +668,8 @@ def bench_apsp(args):
     import paper_1610_10061_amd as pm
     import pmp_inputs as gi
     torch.cuda.set_device(0)
-    peak = ALU_INT32_OPS / 2  # updates/s
+    ops = 1.5  # instructions an update
+    peak = ALU_INT32_OPS / ops  # updates/s
     rows = []
     specs = [(900, 16200, 0), (2000, 8000, 7), (4096, 16384, 1)]
     for n, e, seed in specs:
@@ -696,7 +697,7 @@ def bench_apsp(args):
            "config": {"workload": "APSP of random connected graphs (weights U{1..100}): "
                                   "n=900/16200 edges, n=2000/8000, n=4096/16384"},
            "roofline": {"bound": "alu", "kernel": "k_fw_rest (with k_fw_panels)",
-                        "achieved": big["updates_per_s"] * 2 / 1e12, "peak": ALU_INT32_OPS / 1e12,
+                        "achieved": big["updates_per_s"] * ops / 1e12, "peak": ALU_INT32_OPS / 1e12,
                         "unit": "Tops/s (int32)", "frac": big["frac_of_alu_peak"],
                         "traffic": None},
            "cases": rows}

@@ -385,19 +385,22 @@ PMP_API pmp_status pmp_ga_autotune(pmp_ga *ga, int32_t *clients, int32_t *waves,
  * pmp_batch_autotune  choose the batch evaluation's client tiling by
  *                   timing it: every run keeps its own tuned clients per
  *                   workgroup (scaled to the batch kernel's 16 waves) unless
- *                   one common count of clients per workgroup (64 ... 512;
- *                   fewer for a run whose walks are longer, more for one
- *                   whose partial sums would not fit) is
- *                   faster over the whole batch; the choice goes to
- *                   `*clients` (optional; 0 = each run's own).  The probe
- *                   evaluates each run's generation-0
+ *                   one common count of clients per workgroup (64 ... 512)
+ *                   is faster over the whole batch; the choice goes to
+ *                   `*clients` (optional; 0 = each run's own).  A run whose
+ *                   walks are expected to go past their first 64 entries
+ *                   takes the common count divided by what such a walk costs
+ *                   relative to one that does not, in multiples of 16 and 16
+ *                   at least; a run whose partial sums would not fit takes
+ *                   more.  The probe evaluates each run's generation-0
  *                   population (made again by the first step, identically),
  *                   so every run must be before its first generation
  *                   (PMP_EINVAL otherwise, when the choice is timed).
- *                   Choices are cached per process by the runs'
- *                   shapes.  Results of the runs do not depend on the tiling.  Synchronous on `stream`.  PMP_BATCH_CLIENTS
- *                   sets the common count without timing (also at
- *                   pmp_batch_create).
+ *                   Choices are cached per process by the runs' shapes.
+ *                   Results of the runs do not depend on the tiling.
+ *                   Synchronous on `stream`.  PMP_BATCH_CLIENTS sets the
+ *                   common count (scaled to each run in the same way)
+ *                   without timing, also at pmp_batch_create.
  * pmp_batch_check   wait for `stream`; PMP_EDEVICE if a grid barrier timed
  *                   out (the kernel then drains without finishing); `grid`
  *                   (optional) receives the workgroups of the last launch.
