@@ -382,14 +382,16 @@ int ga_clients_per_block(int n, int P, int m, int p, int W, int waves, bool fuse
 }
 
 // The same of a run in a batch of `beside` chromosome tiles in all, whose
-// stages (a wave per chromosome) add up 64 tiles a round: a CU per workgroup
+// evaluation runs 16 waves and whose stages (a wave per chromosome) add up 64
+// tiles a round: a CU per workgroup
 // while the batch leaves the chip room, never fewer tiles than a round of the
 // run alone.  A generation with one round of the run alone and with this:
 // one run of n = 8000, m = 1000, p = 3, P = 64 1924 and 291 us, two of n = m = 1000,
 // p = 5, P = 128 299 and 174, eight of n = m = 400, p = 20, P = 64 144 and 137; 16
 // of n = m = 1000, p = 4, P = 256 fill the chip (795; 867 with 32 tiles each).
-int batch_clients_per_block(int n, int P, int m, int p, int W, int waves, bool fused, long beside)
+int batch_clients_per_block(int n, int P, int m, int p, int W, bool fused, long beside)
 {
+    constexpr int waves = 16;
     const int cpb = clients_per_block(n, P, m, p, W, false, waves);
     if (env_int("PMP_CLIENTS_PER_BLOCK", 0) > 0)
         return cpb;
@@ -1055,15 +1057,14 @@ hipError_t batch_build(BatchHost &bh, pmp_ga *const *gas, int count)
         it.e.done = nullptr;
         // The batch evaluation runs 16 waves per workgroup: a tile tuned for
         // fewer waves keeps its clients per wave with proportionally more
-        // clients per workgroup (fewer client tiles, so the partial sums
-        // still fit).
-        const int scale = 16 / std::max(1, std::min(16, ga->waves));
+        // clients per workgroup.  No more client tiles than the run's partial
+        // sums have room for, whatever gave the count.
         const pmp_instance *in = ga->inst;
-        const int cpb = ga->tuned ? ga->cpb
-                                  : batch_clients_per_block(in->n, ga->prm.population, in->m,
-                                                            in->p, in->W, ga->waves, ga->fused,
-                                                            beside);
-        bh.base_cpb[b] = cpb * scale;
+        const int cpb =
+            ga->tuned ? ga->cpb * (16 / std::max(1, std::min(16, ga->waves)))
+                      : batch_clients_per_block(in->n, ga->prm.population, in->m, in->p, in->W,
+                                                ga->fused, beside);
+        bh.base_cpb[b] = std::max(cpb, (in->n + ga->part_ti - 1) / ga->part_ti);
         it.X = ga->xstages();
         it.S = it.X + ga->Y;
         it.fb = ga->final_buf();
@@ -2116,7 +2117,7 @@ pmp_status pmp_ga_create(pmp_instance *inst, const pmp_ga_params *prm,
     ga->fcpb = fused_clients_per_block(inst->n, P);
     ga->fTI = (inst->n + ga->fcpb - 1) / ga->fcpb;
     const int batch_cpb =
-        batch_clients_per_block(inst->n, P, inst->m, inst->p, inst->W, ga->waves, ga->fused,
+        batch_clients_per_block(inst->n, P, inst->m, inst->p, inst->W, ga->fused,
                                 (P + kEvalTile - 1) / kEvalTile);
     const int batch_ti = (inst->n + batch_cpb - 1) / batch_cpb;
     const size_t W = inst->W, PW = (size_t)P * W;

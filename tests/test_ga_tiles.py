@@ -97,3 +97,22 @@ print(*[r[2] for r in log("launch") if "k_batch_eval" in r[1]])
     # (one client tile a run)
     tiles = runs * (P // 64)
     assert all(tiles <= int(x) <= 1.125 * tiles + 8 for x in out.split()), (out, tiles)
+
+
+@pytest.mark.parametrize("waves", ["4", "8", "16"])
+def test_batch_tiles_fit_the_partial_sums(tmp_path, waves):
+    """Whatever the batch's rule says when the batch is made (a count set
+    meanwhile, here): no more client tiles than the run has room for."""
+    hip_stub.run(tmp_path, """
+x = instance(900, 900, 90)
+clear()
+g = ga(x, 256)
+room = max(int(r[1]) for r in log("malloc"))  # two sets of 12 bytes a cell
+os.environ["PMP_CLIENTS_PER_BLOCK"] = "4"
+b = batch([g])
+clear()
+ok(pmp.pmp_batch_step(b, 1, None))
+for r in log("launch"):
+    if "k_batch_eval" in r[1]:
+        assert (int(r[2]) - 7) * 64 * 24 <= room, (r, room)
+""", {"PMP_EVAL_WAVES": waves})
